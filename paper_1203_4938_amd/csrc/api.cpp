@@ -218,13 +218,14 @@ bool MixedStep::valid() const {
   // in-line element offsets travel to the passes as 32-bit values
   const int64_t span = (int64_t)(a.mp.L - 1) * std::max(a.in_e, a.out_e);
   return fn_sw[0] && fn_sw[inverse_sw()] && threads > 0 && threads <= 1024 &&
-         threads == a.mp.C * a.mp.T && lds_bytes <= kLdsBytes && a.mp.T * 16 >= a.mp.L &&
+         threads == a.mp.C * a.mp.T && lds_bytes <= kLdsBytes && mixed_covers(a.mp) &&
          span < (int64_t(1) << 31);
 }
 
 std::string MixedStep::describe() const {
   std::ostringstream o;
-  o << name << ": L=" << a.mp.L << " radices=";
+  // the elementary radices of L, then the passes that run them
+  o << name << ": L=" << a.mp.L << " radices=" << mixed_factors(a.mp.L) << " passes=";
   for (int p = 0; p < a.mp.P; ++p) o << (p ? "x" : "") << a.mp.radix[p];
   o << " C=" << a.mp.C << " threads=" << threads << " grid=" << grid.x << " lds=" << lds_bytes
     << "B";
@@ -642,9 +643,10 @@ fft_status_t plan_pow2_2d(dpfft_plan_s *P) {
   return FFT_OK;
 }
 
-// A runtime-radix step over lines of length L, C lines per workgroup.
+// A runtime-radix step over lines of length L, C lines per workgroup (`stream`:
+// a four-step column step writes whole 128-byte lines).
 std::unique_ptr<MixedStep> make_mixed(dpfft_plan_s *P, const char *name, int64_t L, int map,
-                                      int omap, bool tw4, int C) {
+                                      int omap, bool tw4, int C, bool stream = false) {
   auto s = std::make_unique<MixedStep>();
   const Override ov = read_override();
   if (!mixed_radices(L, &s->a.mp, ov.order > 0 ? ov.order : 0)) return nullptr;
@@ -655,8 +657,9 @@ std::unique_ptr<MixedStep> make_mixed(dpfft_plan_s *P, const char *name, int64_t
   s->name = name;
   s->threads = C * s->a.mp.T;
   s->a.mp.tw_lds = mixed_tile_elems(s->a.mp, map, omap);
-  s->lds_bytes = mixed_lds_bytes(s->a.mp, map, omap);
-  for (int sw = 0; sw < 4; ++sw) s->fn_sw[sw] = mixed_kernel(map, omap, tw4, sw);
+  s->lds_bytes = mixed_lds_bytes(s->a.mp, map, omap, tw4);
+  const int tw = !tw4 ? TW4_NONE : C % 16 == 0 && stream ? TW4_STREAM : TW4_PLAIN;
+  for (int sw = 0; sw < 4; ++sw) s->fn_sw[sw] = mixed_kernel(map, omap, tw, sw);
   std::vector<std::complex<double>> lo, hi;
   fourstep_tables(L, s->a.mp.tw2_shift, lo, hi);
   lo.insert(lo.end(), hi.begin(), hi.end());
@@ -665,35 +668,76 @@ std::unique_ptr<MixedStep> make_mixed(dpfft_plan_s *P, const char *name, int64_t
   return s;
 }
 
-// lines per workgroup: as many as keep the workgroup <= `thr` threads and the
-// LDS within one CU's 160 KB, at least `cmin`
-int mixed_lines(int64_t L, int map, int omap, int thr, int cmin) {
+// Most lines per workgroup of a runtime-radix step that its threads (1024)
+// and one CU's LDS allow, 0 if not even one fits.
+int mixed_lines_max(int64_t L, int map, int omap, bool tw4 = false) {
   MixedPlan mp{};
   if (!mixed_radices(L, &mp)) return 0;
-  int C = std::max(cmin, thr / mp.T);
-  while (C > 1) {
-    mp.C = C;
-    if (C * mp.T <= 1024 && mixed_lds_bytes(mp, map, omap) <= kLdsBytes) break;
-    --C;
+  for (mp.C = 1024 / mp.T; mp.C > 0; --mp.C)
+    if (mixed_lds_bytes(mp, map, omap, tw4) <= kLdsBytes) break;
+  return mp.C;
+}
+
+// Lines per workgroup of a row step: the fewest that fill whole waves best
+// (a line's thread count is seldom a multiple of 64).  Small workgroups
+// overlap each other's loads, passes and stores: 3000 points, 16384 lines, 1
+// line per workgroup (167 threads) 176 us, 3 lines 195, 6 lines 250; 960
+// points 51 us at 1 line (64 threads), 55 at 4.
+int mixed_row_lines(int64_t L) {
+  MixedPlan mp{};
+  if (!mixed_radices(L, &mp)) return 0;
+  const int cmax = mixed_lines_max(L, ELEM_FAST, ELEM_FAST);
+  int best = std::min(cmax, 1);
+  double best_score = -1e9;
+  for (int C = 1; C <= cmax; ++C) {
+    const int th = C * mp.T;
+    if (C > 1 && th > 256) break;
+    const double score = th / (64.0 * ((th + 63) / 64)) - 0.02 * std::log2((double)C);
+    if (score > best_score) best_score = score, best = C;
   }
-  mp.C = C;
-  if (C * mp.T > 1024 || mixed_lds_bytes(mp, map, omap) > kLdsBytes) return 0;
+  return best;
+}
+
+// Columns (or transposed rows) per workgroup: 16, so that a row piece is one
+// 128-byte line, where two such workgroups share a CU's LDS, else 8, else 4,
+// else what fits: a workgroup alone on its CU stops its memory traffic while
+// it computes.  46080 = 192 x 240: 16 columns 160 + 143 us, 8 columns 204 +
+// 156; 1080-point columns (16 of them: one workgroup per CU): 142 us at 16,
+// 106 at 8; 1000 x 1000 four-step: 306 + 275 us at 16, 263 + 223 at 8.
+int mixed_col_lines(int64_t L, int map, bool tw4 = false) {
+  const int omap = LINE_FAST;
+  const int cmax = mixed_lines_max(L, map, omap, tw4);
+  MixedPlan mp{};
+  if (!mixed_radices(L, &mp)) return 0;
+  for (mp.C = 16; mp.C >= 4; mp.C /= 2)
+    if (mp.C <= cmax && 2 * mixed_lds_bytes(mp, map, omap, tw4) <= kLdsBytes) return mp.C;
+  int C = 8;
+  while (C > cmax) C /= 2;
   return C;
+}
+
+// lines per workgroup of step i: the override's where it fits, else `def`
+int mixed_c(const Override &ov, int i, int def, int64_t L, int map, int omap, bool tw4 = false) {
+  return ov.c[i] > 0 && ov.c[i] <= mixed_lines_max(L, map, omap, tw4) ? ov.c[i] : def;
 }
 
 // The two launches of an N-point 7-smooth four-step over B signals, in_b
 // and out_b elements apart in the caller's input and output (pass A: input
 // -> workspace with the twiddle; pass B: workspace -> output, transposed).
+// `pitch`: elements between the rows of the intermediate (at least N2; 0 =
+// N2, dense).
 bool mixed_fourstep_steps(dpfft_plan_s *P, int64_t N, int64_t B, int64_t in_b, int64_t out_b,
-                          std::unique_ptr<MixedStep> &a, std::unique_ptr<MixedStep> &b) {
+                          int64_t pitch, std::unique_ptr<MixedStep> &a,
+                          std::unique_ptr<MixedStep> &b) {
   const int64_t N1 = split_factor(N), N2 = N / N1;
+  if (pitch == 0) pitch = N2;
   if (N2 > kSinglePassMax) return false;
-  const int CA = mixed_lines(N1, LINE_FAST, LINE_FAST, 1024, 1);
-  const int CB = mixed_lines(N2, ELEM_FAST, LINE_FAST, 1024, 1);
-  a = CA ? make_mixed(P, "mixed_fourstep_columns", N1, LINE_FAST, LINE_FAST, true, std::min(CA, 16))
+  const Override ov = read_override();
+  const int CA = mixed_c(ov, 0, mixed_col_lines(N1, LINE_FAST, true), N1, LINE_FAST, LINE_FAST, true);
+  const int CB = mixed_c(ov, 1, mixed_col_lines(N2, ELEM_FAST), N2, ELEM_FAST, LINE_FAST);
+  a = CA ? make_mixed(P, "mixed_fourstep_columns", N1, LINE_FAST, LINE_FAST, true, CA, pitch % 16 == 0)
          : nullptr;
-  b = CB ? make_mixed(P, "mixed_fourstep_rows_transposed", N2, ELEM_FAST, LINE_FAST, false,
-                      std::min(CB, 16))
+  b = CB ? make_mixed(P, "mixed_fourstep_rows_transposed", N2, ELEM_FAST, LINE_FAST, false, CB)
          : nullptr;
   if (!a || !b) return false;
   std::vector<std::complex<double>> lo, hi;
@@ -705,9 +749,9 @@ bool mixed_fourstep_steps(dpfft_plan_s *P, int64_t N, int64_t B, int64_t in_b, i
   a->a.in_b = in_b;
   a->a.in_l = 1;
   a->a.in_e = N2;
-  a->a.out_b = N;
+  a->a.out_b = N1 * pitch;
   a->a.out_l = 1;
-  a->a.out_e = N2;
+  a->a.out_e = pitch;
   a->a.lines = N2;
   a->a.tiles_per_batch = (N2 + a->a.mp.C - 1) / a->a.mp.C;
   a->a.flags = F_REMAP;
@@ -715,8 +759,8 @@ bool mixed_fourstep_steps(dpfft_plan_s *P, int64_t N, int64_t B, int64_t in_b, i
   a->first = true;
   a->src = BUF_IN;
   a->dst = BUF_WS;
-  b->a.in_b = N;
-  b->a.in_l = N2;
+  b->a.in_b = N1 * pitch;
+  b->a.in_l = pitch;
   b->a.in_e = 1;
   b->a.out_b = out_b;
   b->a.out_l = 1;
@@ -740,11 +784,11 @@ bool mixed_fourstep_steps(dpfft_plan_s *P, int64_t N, int64_t B, int64_t in_b, i
 // butterfly of one thread.
 fft_status_t plan_mixed_2d(dpfft_plan_s *P) {
   const int64_t NY = P->ny, NX = P->nx, B = P->batch, D = P->dist;
-  const int CR = mixed_lines(NX, ELEM_FAST, ELEM_FAST, 256, 1);
-  const int CC = mixed_lines(NY, LINE_FAST, LINE_FAST, 1024, 1);
+  const Override ov = read_override();
+  const int CR = mixed_c(ov, 0, mixed_row_lines(NX), NX, ELEM_FAST, ELEM_FAST);
+  const int CC = mixed_c(ov, 1, mixed_col_lines(NY, LINE_FAST), NY, LINE_FAST, LINE_FAST);
   auto r = CR ? make_mixed(P, "mixed_rows", NX, ELEM_FAST, ELEM_FAST, false, CR) : nullptr;
-  auto c = CC ? make_mixed(P, "mixed_columns", NY, LINE_FAST, LINE_FAST, false, std::min(CC, 16))
-              : nullptr;
+  auto c = CC ? make_mixed(P, "mixed_columns", NY, LINE_FAST, LINE_FAST, false, CC) : nullptr;
   if (!r || !c) return fail(FFT_E_UNSUPPORTED, "no runtime-radix 2D kernels for this shape");
   r->a.in_b = r->a.out_b = D;
   r->a.in_l = r->a.out_l = NX;
@@ -776,9 +820,9 @@ fft_status_t plan_mixed_1d(dpfft_plan_s *P) {
   const int64_t N = P->n, B = P->batch, D = P->dist;
   const Override ov = read_override();
   if (N <= kSinglePassMax) {
-    int C = mixed_lines(N, ELEM_FAST, ELEM_FAST, 256, 1);
+    int C = mixed_row_lines(N);
     if (ov.c[0] > 0) {
-      const int cmax = mixed_lines(N, ELEM_FAST, ELEM_FAST, 1024, 1);
+      const int cmax = mixed_lines_max(N, ELEM_FAST, ELEM_FAST);
       if (ov.c[0] > cmax) return fail(FFT_E_UNSUPPORTED, "override c0 too large for N");
       C = ov.c[0];
     }
@@ -797,12 +841,17 @@ fft_status_t plan_mixed_1d(dpfft_plan_s *P) {
     return FFT_OK;
   }
   std::unique_ptr<MixedStep> a, b;
-  if (!mixed_fourstep_steps(P, N, B, D, D, a, b))
+  // rows of the intermediate on whole 128-byte lines, unless only the dense
+  // workspace fits the library's own scratch array
+  const int64_t N1 = split_factor(N), N2 = N / N1;
+  const auto ws_of = [&](int64_t p) { return (size_t)B * (size_t)(N1 * p) * sizeof(float2); };
+  int64_t pitch = (N2 + 15) / 16 * 16;
+  if (ws_of(pitch) > kScratchBytes && ws_of(N2) <= kScratchBytes) pitch = N2;
+  if (!mixed_fourstep_steps(P, N, B, D, D, pitch, a, b))
     return fail(FFT_E_UNSUPPORTED, "no mixed four-step plan for N=" + std::to_string(N));
-  const int64_t N1 = a->a.mp.L, N2 = b->a.mp.L;
   P->steps.push_back(std::move(a));
   P->steps.push_back(std::move(b));
-  P->ws_bytes = (size_t)B * (size_t)N * sizeof(float2);
+  P->ws_bytes = ws_of(pitch);
   P->variant = "mixed four-step " + std::to_string(N1) + "x" + std::to_string(N2);
   return FFT_OK;
 }
@@ -1019,8 +1068,7 @@ fft_status_t plan_real_1d(dpfft_plan_s *P) {
     if (L <= kSinglePassMax && !is_pow2(L)) {
       // single-pass runtime-radix core: input -> workspace (forward), and
       // workspace -> output after the pairing (inverse), never in place
-      int C = mixed_lines(L, ELEM_FAST, ELEM_FAST, 256, 1);
-      if (ov.c[0] > 0 && ov.c[0] <= mixed_lines(L, ELEM_FAST, ELEM_FAST, 1024, 1)) C = ov.c[0];
+      const int C = mixed_c(ov, 0, mixed_row_lines(L), L, ELEM_FAST, ELEM_FAST);
       std::unique_ptr<MixedStep> c[2];
       for (int i = 0; i < 2; ++i) {
         c[i] = C ? make_mixed(P, i ? "real_core_rows_inverse" : "real_core_rows", L, ELEM_FAST,
@@ -1067,7 +1115,7 @@ fft_status_t plan_real_1d(dpfft_plan_s *P) {
         a = std::move(x[0]), b = std::move(x[1]), ai = std::move(x[2]), bi = std::move(x[3]);
       } else {
         std::unique_ptr<MixedStep> x[4];
-        if (!mixed_fourstep_steps(P, L, B, L, L, x[0], x[1]) || !mixed_fourstep_steps(P, L, B, L, L, x[2], x[3]))
+        if (!mixed_fourstep_steps(P, L, B, L, L, 0, x[0], x[1]) || !mixed_fourstep_steps(P, L, B, L, L, 0, x[2], x[3]))
           return fail(FFT_E_UNSUPPORTED, "no four-step core for real N=" + std::to_string(N));
         const char *nm[4] = {"real_core_columns", "real_core_rows_transposed",
                              "real_core_columns_inverse", "real_core_rows_transposed_inverse"};
@@ -1115,15 +1163,15 @@ fft_status_t plan_real_1d(dpfft_plan_s *P) {
 fft_status_t plan_real_2d_mixed(dpfft_plan_s *P) {
   const int64_t NY = P->ny, NX = P->nx, B = P->batch;
   const int64_t L = NX / 2, W = L + 1, R = B * NY;
-  const int CR = mixed_lines(L, ELEM_FAST, ELEM_FAST, 256, 1);
-  const int CC = mixed_lines(NY, LINE_FAST, LINE_FAST, 1024, 1);
+  const Override ov = read_override();
+  const int CR = mixed_c(ov, 0, mixed_row_lines(L), L, ELEM_FAST, ELEM_FAST);
+  const int CC = mixed_c(ov, 1, mixed_col_lines(NY, LINE_FAST), NY, LINE_FAST, LINE_FAST);
   std::unique_ptr<MixedStep> row[2], col[2];
   for (int i = 0; i < 2; ++i) {
     row[i] = CR ? make_mixed(P, i ? "real_core_rows_inverse" : "real_core_rows", L, ELEM_FAST,
                              ELEM_FAST, false, CR)
                 : nullptr;
-    col[i] = CC ? make_mixed(P, i ? "columns_inverse" : "columns", NY, LINE_FAST, LINE_FAST, false,
-                             std::min(CC, 16))
+    col[i] = CC ? make_mixed(P, i ? "columns_inverse" : "columns", NY, LINE_FAST, LINE_FAST, false, CC)
                 : nullptr;
     if (!row[i] || !col[i])
       return fail(FFT_E_UNSUPPORTED, "no runtime-radix kernels for this real-input image");

@@ -1,5 +1,5 @@
 // Device building blocks for the gfx950 FFT kernels: complex arithmetic and
-// in-register DFTs of radix 2, 3, 4, 5, 7, 8, 16 and 32.
+// in-register DFTs of radix 2..10, 12, 14, 15, 16, 18, 20, 21, 24, 25 and 32.
 //
 // Every DFT here is the forward transform X[k] = sum_j x[j] w_R^{jk} with
 // w_R = exp(-2 pi i / R), computed in place in natural order.  The inverse
@@ -10,6 +10,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <numeric>
 #include <utility>
 
 namespace dpfft {
@@ -122,6 +123,30 @@ __device__ __forceinline__ cf mulw9(cf x) {
   }
 }
 
+// x * w_25^E: cos and sin of 2*pi*e/25, e = 0..24
+__device__ constexpr float kCos25[25] = {
+    1.000000000000000000f, 0.968583161128631076f, 0.876306680043863584f, 0.728968627421411552f, 0.535826794978996546f,
+    0.309016994374947451f, 0.062790519529313527f, -0.187381314585724601f, -0.425779291565072715f, -0.637423989748689745f,
+    -0.809016994374947340f, -0.929776485888251347f, -0.992114701314477765f, -0.992114701314477876f, -0.929776485888251458f,
+    -0.809016994374947784f, -0.637423989748689523f, -0.425779291565072160f, -0.187381314585724629f, 0.062790519529312833f,
+    0.309016994374947229f, 0.535826794978996768f, 0.728968627421411219f, 0.876306680043863140f, 0.968583161128630965f};
+__device__ constexpr float kSin25[25] = {
+    0.000000000000000000f, 0.248689887164854795f, 0.481753674101715323f, 0.684547105928688615f, 0.844327925502015075f,
+    0.951056516295153531f, 0.998026728428271559f, 0.982287250728688721f, 0.904827052466019466f, 0.770513242775789253f,
+    0.587785252292473248f, 0.368124552684678141f, 0.125333233564304536f, -0.125333233564304286f, -0.368124552684677919f,
+    -0.587785252292472693f, -0.770513242775789364f, -0.904827052466019799f, -0.982287250728688721f, -0.998026728428271559f,
+    -0.951056516295153642f, -0.844327925502014964f, -0.684547105928688948f, -0.481753674101716101f, -0.248689887164855350f};
+template <int E>
+__device__ __forceinline__ cf mulw25(cf x) {
+  constexpr int e = ((E % 25) + 25) % 25;
+  if constexpr (e == 0) {
+    return x;
+  } else {
+    constexpr float c = kCos25[e], s = kSin25[e];  // w = c - i s
+    return make_float2(x.x * c + x.y * s, x.y * c - x.x * s);
+  }
+}
+
 // ---------------------------------------------------------------------------
 // power-of-two DFTs
 // ---------------------------------------------------------------------------
@@ -165,6 +190,8 @@ __device__ __forceinline__ void twiddle_row(cf *b) {
         ((b[K] = mulw16<R1 * R2, N2 * K>(b[K])), ...);
       else if constexpr (R1 * R2 == 9)
         ((b[K] = mulw9<N2 * K>(b[K])), ...);
+      else if constexpr (R1 * R2 == 25)
+        ((b[K] = mulw25<N2 * K>(b[K])), ...);
       else
         ((b[K] = mulw32<R1 * R2, N2 * K>(b[K])), ...);
     }(std::make_integer_sequence<int, R1>{});
@@ -273,10 +300,55 @@ template <> struct Dft<5> {
 template <> struct Dft<7> {
   __device__ __forceinline__ static void run(cf *a) { dft_prime<7>(a); }
 };
-// DFT-9 as 3 x 3: two passes of 3 fewer through LDS for every pair of 3s
+// DFT-9 as 3 x 3 and DFT-25 as 5 x 5: one pass through LDS fewer for every
+// pair of 3s or 5s
 template <> struct Dft<9> {
   __device__ __forceinline__ static void run(cf *a) { dft_two_factor<3, 3>(a); }
 };
+template <> struct Dft<25> {
+  __device__ __forceinline__ static void run(cf *a) { dft_two_factor<5, 5>(a); }
+};
+
+// DFT of R = R1 R2 points, R1 and R2 coprime, without twiddles (Good and
+// Thomas): with inputs n = R2 n1 + R1 n2 (mod R) and outputs k by the Chinese
+// remainder theorem, k = k1 (mod R1) = k2 (mod R2),
+//   w_R^{n k} = w_R1^{n1 k} w_R2^{n2 k} = w_R1^{n1 k1} w_R2^{n2 k2}.
+template <int R1, int R2>
+__device__ __forceinline__ void dft_coprime(cf *a) {
+  static_assert(std::gcd(R1, R2) == 1, "coprime factors");
+  constexpr int R = R1 * R2;
+  cf b[R2][R1];
+#pragma unroll
+  for (int n2 = 0; n2 < R2; ++n2) {
+#pragma unroll
+    for (int n1 = 0; n1 < R1; ++n1) b[n2][n1] = a[(R2 * n1 + R1 * n2) % R];
+    Dft<R1>::run(b[n2]);
+  }
+#pragma unroll
+  for (int k1 = 0; k1 < R1; ++k1) {
+    cf c[R2];
+#pragma unroll
+    for (int n2 = 0; n2 < R2; ++n2) c[n2] = b[n2][k1];
+    Dft<R2>::run(c);
+    // k = k1 + R1 t, t = 0..R2-1, meets every residue k2 = k mod R2 once
+#pragma unroll
+    for (int t = 0; t < R2; ++t) a[k1 + R1 * t] = c[(k1 + R1 * t) % R2];
+  }
+}
+#define DPFFT_DFT_COPRIME(R_, A_, B_)                                              \
+  template <> struct Dft<R_> {                                                     \
+    __device__ __forceinline__ static void run(cf *a) { dft_coprime<A_, B_>(a); }  \
+  };
+DPFFT_DFT_COPRIME(6, 3, 2)
+DPFFT_DFT_COPRIME(10, 5, 2)
+DPFFT_DFT_COPRIME(12, 3, 4)
+DPFFT_DFT_COPRIME(14, 7, 2)
+DPFFT_DFT_COPRIME(15, 5, 3)
+DPFFT_DFT_COPRIME(18, 9, 2)
+DPFFT_DFT_COPRIME(20, 5, 4)
+DPFFT_DFT_COPRIME(21, 7, 3)
+DPFFT_DFT_COPRIME(24, 3, 8)
+#undef DPFFT_DFT_COPRIME
 
 // ---------------------------------------------------------------------------
 // workgroup -> tile remapping that keeps consecutive tiles on one XCD.

@@ -17,6 +17,9 @@ constexpr int64_t kMaxN = int64_t(1) << 24;
 constexpr int kSinglePassMax = 16384;  // longest line one workgroup transforms
 constexpr int kLdsBytes = 160 * 1024;  // LDS of one CU
 
+// Bytes of the library's own workspace array (fft_exec_noalloc): 8 Mi complex64.
+constexpr size_t kScratchBytes = size_t(64) << 20;
+
 // Record `msg` as this thread's last error and return `s`.
 fft_status_t fail(fft_status_t s, const std::string &msg);
 

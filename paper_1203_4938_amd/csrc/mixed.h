@@ -1,16 +1,18 @@
-// Runtime-radix (mixed 2/3/4/5/7/8/9/16) Stockham transforms: argument blocks
-// shared by the host planner and the device code.
+// Runtime-radix Stockham transforms of 7-smooth lengths (radices of
+// mixed_plan.h): argument blocks shared by the host planner and the device
+// code.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <string>
+
+#include "mixed_plan.h"
+
 namespace dpfft {
 
-constexpr int kMaxPasses = 12;
-
 // Radix plan of one line length L = prod radix[p].  Thread j of a line owns
-// butterflies b = j + T*q of every pass; T >= ceil(L/16) bounds the
-// butterflies of a pass to ceil(16/R) per thread.
+// butterflies b = j + T*q of every pass, at most mixed_qmax(R) of them.
 struct MixedPlan {
   int32_t L;
   int32_t P;                  // passes
@@ -38,18 +40,32 @@ struct MixedArgs {
   uint32_t flags;
 };
 
-// Host: radix sequence for a 7-smooth L.  order 0: 16s, then 8/4/2, then 7,
-// 5, 9 (pairs of 3), 3; order 1: the odd radices first, then the powers of
-// two.  Returns false if L has a prime factor above 7 or needs too many
-// passes.
-bool mixed_radices(int64_t L, MixedPlan *mp, int order = 0);
+// Host: radix plan of a 7-smooth L (radix_plan of mixed_plan.h) with at most
+// tmax threads per line; order 0: largest radix first, 1: smallest first.
+// Returns false if L has a prime factor above 7 or no plan within tmax.
+bool mixed_radices(int64_t L, MixedPlan *mp, int order = 0, int tmax = 1024);
 
-// Host: the kernel instance for (map, omap, tw4, swap mode); nullptr if none.
-const void *mixed_kernel(int map, int omap, bool tw4, int sw);
+// Host: whether every pass's butterflies are owned by the plan's threads.
+bool mixed_covers(const MixedPlan &mp);
+
+// Host: the factorization of a 7-smooth L into the elementary radices (16s,
+// then 8/4/2, then 7, 5, 9 for pairs of 3, 3), as "16x7x3"; the passes run
+// products of them.
+std::string mixed_factors(int64_t L);
+
+// Four-step twiddle of a column step: none, applied, applied with streamed
+// stores (tiles of whole 128-byte lines only: with 64-byte pieces, 8 columns
+// of 1000 x 1000, they took 281 us against 268).
+enum : int { TW4_NONE = 0, TW4_PLAIN = 1, TW4_STREAM = 2 };
+
+// Host: the kernel instance for (map, omap, TW4_*, swap mode); nullptr if none.
+const void *mixed_kernel(int map, int omap, int tw4, int sw);
 
 // LDS elements of the tile data of a workgroup, and total LDS bytes (tile
-// data plus the pass-twiddle table that follows it).
+// data, the pass-twiddle table that follows it and, for column tiles with the
+// four-step twiddle, kFourStepVals values per line).
+constexpr int kFourStepVals = 5;
 int mixed_tile_elems(const MixedPlan &mp, int map, int omap);
-int mixed_lds_bytes(const MixedPlan &mp, int map, int omap);
+int mixed_lds_bytes(const MixedPlan &mp, int map, int omap, bool tw4);
 
 }  // namespace dpfft

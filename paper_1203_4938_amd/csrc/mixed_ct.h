@@ -49,8 +49,9 @@ struct CtArgs {
 // The first pass also stores this thread's entry `tv` of the pass-twiddle
 // table (loaded by the caller before the tile's data loads) at twl[tid]
 // once its data loads are issued; its closing barrier publishes the table.
-template <int L, int PP, int MAP, int OMAP, bool TW4, int SW>
-__device__ __forceinline__ void ct_pass(const CtArgs &a, lcf *lds, lcf *twl, cf tv) {
+template <int L, int PP, int MAP, int OMAP, bool TW4, int SW, class F4>
+__device__ __forceinline__ void ct_pass(const CtArgs &a, lcf *lds, lcf *twl, cf tv,
+                                        const F4 &f4) {
   using PL = CtPlan<L>;
   constexpr int R = PL::R(PP), NS = PL::NS(PP), M = L / R, T = PL::T;
   constexpr int QM = (M + T - 1) / T;
@@ -87,6 +88,13 @@ __device__ __forceinline__ void ct_pass(const CtArgs &a, lcf *lds, lcf *twl, cf 
       for (int r = 1; r < R; ++r) v[q][r] = cmul(v[q][r], ldc(twl, TWO + (r - 1) * NS + k));
     }
     Dft<R>::run(v[q]);
+    if constexpr (TW4 && LAST) {
+      f4.apply(v[q], q, twl + PL::NTW + a.c, a.C);  // outputs k1 = b + r NS
+    }
+    if constexpr ((SW & 2) && LAST) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) v[q][r] = cswap(cscale(v[q][r], a.scale));
+    }
   }
   if constexpr (!FIRST) __syncthreads();  // every read of this pass precedes the in-place writes
 #pragma unroll
@@ -95,50 +103,26 @@ __device__ __forceinline__ void ct_pass(const CtArgs &a, lcf *lds, lcf *twl, cf 
     const int b = a.j + T * q;
     const int k = NS > 1 ? b % NS : 0;
     const int base = (b - k) * R + k;
-    cf tw[R];
-    if constexpr (TW4 && LAST) {
-      // outputs k1 = b + r NS: w_N^{line k1} = A B^r, A = w_N^{line b}, B = w_N^{line NS}
-      const uint32_t msk = (1u << a.tw4_shift) - 1u;
-      const uint32_t ea = a.line * (uint32_t)b, eb = a.line * (uint32_t)NS;
-      const cf A = cmul(ldc(a.tw4_hi, ea >> a.tw4_shift), ldc(a.tw4_lo, ea & msk));
-      const cf B = cmul(ldc(a.tw4_hi, eb >> a.tw4_shift), ldc(a.tw4_lo, eb & msk));
-      // B^r from repeated squares (depth <= 4), as the runtime passes form it
-      cf Bp[R];
-      Bp[0] = make_float2(1.0f, 0.0f);
-      if constexpr (R > 1) Bp[1] = B;
-#pragma unroll
-      for (int r = 2; r < R; ++r) {
-        int p2 = 1;
-        while (2 * p2 <= r) p2 *= 2;
-        Bp[r] = (r == p2) ? cmul(Bp[p2 / 2], Bp[p2 / 2]) : cmul(Bp[p2], Bp[r - p2]);
-      }
-      tw[0] = A;
-#pragma unroll
-      for (int r = 1; r < R; ++r) tw[r] = cmul(A, Bp[r]);
-    }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       const int pos = base + r * NS;
-      cf y = v[q][r];
-      if constexpr (LAST) {
-        if constexpr (TW4) y = cmul(y, tw[r]);
-        if constexpr (SW & 2) y = cswap(cscale(y, a.scale));
-        if constexpr (OMAP == MAP)
-          stc(a.dst, (uint32_t)pos * a.out_e, y);
-        else
-          stc(lds, ct_idx<L, OMAP>(a.C, a.c, pos), y);
-      } else {
-        stc(lds, ct_idx<L, MAP>(a.C, a.c, pos), y);
-      }
+      if constexpr (LAST && TW4)
+        stc_nt(a.dst, (uint32_t)pos * a.out_e, v[q][r]);  // streamed, as mixed_pass
+      else if constexpr (LAST && OMAP == MAP)
+        stc(a.dst, (uint32_t)pos * a.out_e, v[q][r]);
+      else if constexpr (LAST)
+        stc(lds, ct_idx<L, OMAP>(a.C, a.c, pos), v[q][r]);
+      else
+        stc(lds, ct_idx<L, MAP>(a.C, a.c, pos), v[q][r]);
     }
   }
   if constexpr (!LAST || OMAP != MAP) __syncthreads();
 }
 
-template <int L, int MAP, int OMAP, bool TW4, int SW, int... PP>
-__device__ __forceinline__ void ct_passes(const CtArgs &a, lcf *lds, lcf *twl, cf tv,
+template <int L, int MAP, int OMAP, bool TW4, int SW, class F4, int... PP>
+__device__ __forceinline__ void ct_passes(const CtArgs &a, lcf *lds, lcf *twl, cf tv, const F4 &f4,
                                           std::integer_sequence<int, PP...>) {
-  (ct_pass<L, PP, MAP, OMAP, TW4, SW>(a, lds, twl, tv), ...);
+  (ct_pass<L, PP, MAP, OMAP, TW4, SW>(a, lds, twl, tv, f4), ...);
 }
 
 // One tile through every pass.  `tw` is the per-pass table in global memory,
@@ -178,7 +162,20 @@ __device__ __noinline__ void ct_tile(const gcf *src, gcf *dst, gcf *dst2, const 
   for (int i = threadIdx.x + nthreads; i < PL::NTW; i += nthreads) stc(twl, i, ldc(tw, i));
   cf tv = make_float2(0.0f, 0.0f);
   if ((int)threadIdx.x < PL::NTW && (int)threadIdx.x < nthreads) tv = ldc(tw, threadIdx.x);
-  ct_passes<L, MAP, OMAP, TW4, SW>(a, lds, twl, tv, std::make_integer_sequence<int, PL::P>{});
+  // four-step twiddle entries of the last pass, in flight with the data
+  constexpr int RL = PL::R(PL::P - 1), ML = L / RL;
+  FourStepTw<RL, (ML + PL::T - 1) / PL::T> f4;
+  if constexpr (TW4) {
+    f4.load(a.tw4_lo, a.tw4_hi, a.tw4_shift, a.valid ? a.line : 0u, (uint32_t)a.j,
+            (uint32_t)PL::T, (uint32_t)ML);
+    static_assert(PL::P > 1, "the first pass's barrier publishes the values");
+    // (in_e lines of the matrix: its rows are that long)
+    four_step_fill(twl + PL::NTW, a.tw4_lo, a.tw4_hi, a.tw4_shift, a.C,
+                   (uint32_t)__builtin_amdgcn_readfirstlane((int)(a.line - (uint32_t)a.c)), a.in_e,
+                   (uint32_t)L, (uint32_t)PL::NS(PL::P - 1), (uint32_t)PL::T, (int)threadIdx.x,
+                   nthreads);
+  }
+  ct_passes<L, MAP, OMAP, TW4, SW>(a, lds, twl, tv, f4, std::make_integer_sequence<int, PL::P>{});
   if constexpr (OMAP != MAP) {
     if (a.valid2) {
 #pragma unroll 4

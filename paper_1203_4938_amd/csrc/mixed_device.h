@@ -32,6 +32,14 @@ __device__ __forceinline__ void stc(P *p, I i, cf y) {
   p[i] = v;
 }
 
+// a streamed store (whole lines of data that is read again only much later)
+__device__ __forceinline__ void stc_nt(gcf *p, uint32_t i, cf y) {
+  v2f v;
+  v.x = y.x;
+  v.y = y.y;
+  __builtin_nontemporal_store(v, p + i);
+}
+
 namespace {
 
 __device__ __forceinline__ int midx_elem(int pitch, int c, int pos) {
@@ -48,22 +56,25 @@ __device__ __forceinline__ cf tw2_lookup(const lcf *t, int shift, uint32_t e) {
   return cmul(hi, lo);
 }
 
-// Pass twiddles w_L^{e1 r}, r = 1..R-1, into x[1..R-1] (multiplied in).  For
-// R = 8 and 16 only r = 1, 2, 3 and the multiples of 4 are looked up; the
+// Pass twiddles w_L^{e1 r}, r = 1..R-1, into x[1..R-1] (multiplied in).  From
+// radix 6 on only r = 1, 2, 3 and the multiples of 4 are looked up; the
 // others are products w^{4s} w^{l}, which halves the table reads.
 template <int R>
 __device__ __forceinline__ void apply_pass_twiddles(cf *x, const lcf *t, int shift, uint32_t e1) {
-  if constexpr (R == 8 || R == 16) {
-    cf wl[4], w4[R / 4];
+  if constexpr (R >= 6) {
+    cf wl[4];
 #pragma unroll
-    for (int l = 1; l < 4; ++l) wl[l] = tw2_lookup(t, shift, e1 * (uint32_t)l);
+    for (int l = 1; l < 4; ++l) {
+      wl[l] = tw2_lookup(t, shift, e1 * (uint32_t)l);
+      x[l] = cmul(x[l], wl[l]);
+    }
 #pragma unroll
-    for (int s = 1; s < R / 4; ++s) w4[s] = tw2_lookup(t, shift, e1 * (uint32_t)(4 * s));
+    for (int s = 4; s < R; s += 4) {
+      const cf w4 = tw2_lookup(t, shift, e1 * (uint32_t)s);
+      x[s] = cmul(x[s], w4);
 #pragma unroll
-    for (int r = 1; r < R; ++r) {
-      const int s = r / 4, l = r % 4;
-      const cf w = s == 0 ? wl[l] : (l == 0 ? w4[s] : cmul(w4[s], wl[l]));
-      x[r] = cmul(x[r], w);
+      for (int l = 1; l < 4; ++l)
+        if (s + l < R) x[s + l] = cmul(x[s + l], cmul(w4, wl[l]));
     }
   } else {
 #pragma unroll
@@ -71,30 +82,95 @@ __device__ __forceinline__ void apply_pass_twiddles(cf *x, const lcf *t, int shi
   }
 }
 
-__device__ __forceinline__ cf tw4_lookup_m(const MixedArgs &a, uint32_t e) {
-  const uint32_t lo = e & ((1u << a.tw4_shift) - 1u);
-  const uint32_t hi = e >> a.tw4_shift;
-  return cmul(a.tw4_hi[hi], a.tw4_lo[lo]);
+// Four-step twiddles w_N^{line (b + r NS)} = A B^r of outputs r = 0..R-1 of
+// butterfly b = j + T q: A B^l for l < 4 from A and B, times B^{4 g}, with
+// B^4, B^8 and B^16 taken from the two-level table of w_N as well (the error
+// of B would grow with the power), so at most three products follow a lookup.
+// All but A depend on the line alone: kFourStepVals values per line, looked up
+// once per tile by its first threads and kept in LDS, where every lane of the
+// line reads the same word.  As per-lane gathers (a dozen cache lines each)
+// they cost more than the tile's data loads: 46080 = 192 x 240, 72 M points,
+// the column launch 275 us with gathers after the butterflies, 259 with
+// gathers issued early, 230 so.
+// The values of `C` lines from line0 on at tab[v * C + c]: w_N^{line m}, m =
+// ns, 4 ns, 8 ns, 16 ns and T, as far as a line of L outputs needs them (m < L
+// keeps line * m below N).
+__device__ __forceinline__ void four_step_fill(lcf *tab, const gcf *lo, const gcf *hi, int shift,
+                                               int C, uint32_t line0, uint32_t lines, uint32_t L,
+                                               uint32_t ns, uint32_t T, int tid, int nth) {
+  for (int t = tid; t < kFourStepVals * C; t += nth) {
+    const int v = t / C;
+    const uint32_t line = line0 + (uint32_t)(t - v * C);
+    const uint32_t m = v == 0 ? ns : v == 1 ? 4 * ns : v == 2 ? 8 * ns : v == 3 ? 16 * ns : T;
+    if (m >= L || line >= lines) continue;
+    const uint32_t e = line * m;
+    stc(tab, t, cmul(ldc(hi, e >> shift), ldc(lo, e & ((1u << shift) - 1u))));
+  }
 }
+
+template <int R, int Q>
+struct FourStepTw {
+  cf ah[(Q + 1) / 2], al[(Q + 1) / 2];  // table entries of A for even q
+  __device__ __forceinline__ void load(const gcf *lo, const gcf *hi, int shift, uint32_t line,
+                                       uint32_t j, uint32_t T, uint32_t M) {
+#pragma unroll
+    for (int q = 0; q < Q; q += 2) {
+      const uint32_t b = j + T * (uint32_t)q;
+      const uint32_t e = line * (b < M ? b : 0u);
+      ah[q / 2] = ldc(hi, e >> shift);
+      al[q / 2] = ldc(lo, e & ((1u << shift) - 1u));
+    }
+  }
+  // multiply butterfly q's outputs; tab points at the line's first value
+  __device__ __forceinline__ void apply(cf *x, int q, const lcf *tab, int C) const {
+    cf a = cmul(ah[q / 2], al[q / 2]);
+    if (q & 1) a = cmul(a, ldc(tab, 4 * C));
+    cf Al[4] = {a, a, a, a};
+    if constexpr (R > 1) {
+      const cf b = ldc(tab, 0);
+      Al[1] = cmul(a, b);
+      if constexpr (R > 2) {
+        const cf b2 = cmul(b, b);
+        Al[2] = cmul(a, b2);
+        if constexpr (R > 3) Al[3] = cmul(a, cmul(b2, b));
+      }
+    }
+    cf p4 = a, p8 = a, p16 = a;
+    if constexpr (R > 4) p4 = ldc(tab, C);
+    if constexpr (R > 8) p8 = ldc(tab, 2 * C);
+    if constexpr (R > 16) p16 = ldc(tab, 3 * C);
+#pragma unroll
+    for (int l = 0; l < 4 && l < R; ++l) x[l] = cmul(x[l], Al[l]);
+#pragma unroll
+    for (int g = 1; 4 * g < R; ++g) {
+      cf w = g & 1 ? p4 : g & 2 ? p8 : p16;
+      if ((g & 1) && (g & 2)) w = cmul(w, p8);
+      if ((g & 3) && (g & 4)) w = cmul(w, p16);
+#pragma unroll
+      for (int l = 0; l < 4; ++l)
+        if (4 * g + l < R) x[4 * g + l] = cmul(x[4 * g + l], cmul(Al[l], w));
+    }
+  }
+};
 
 }  // namespace
 
 // One pass.  It is a separate (non-inlined) function per radix so that each
 // radix gets its own register allocation; its context travels as plain
 // scalars and address-space-qualified pointers.  `tw2` is the two-level
-// table of w_L held in LDS.
+// table of w_L held in LDS.  `sw` is the launch's swap mode.
 // The first pass also copies the first `ntw` entries of the global table tw2g
 // into tw2 (one per thread): their loads are issued before the tile's data
 // loads and their LDS stores after them, so the copy adds no round trip of its
 // own (the pass's closing barrier publishes the table to the later passes).
-template <int MAP, int OMAP, bool TW4, int SW, int R>
+template <int MAP, int OMAP, int TW4, int R>
 __device__ __noinline__ void mixed_pass(const gcf *__restrict__ src, gcf *__restrict__ dst,
                                         lcf *lds, lcf *tw2, const gcf *__restrict__ tw2g, int ntw,
                                         const gcf *__restrict__ tw4_lo,
-                                        const gcf *__restrict__ tw4_hi, int L, int T, int C,
-                                        int pitch, int NS, int tw2_shift, int tw4_shift, int c,
-                                        int j, bool valid, bool first, bool last, int64_t in_e,
-                                        int64_t out_e, int64_t line, float scale) {
+                                        const gcf *__restrict__ tw4_hi, lcf *tw4_tab, int L,
+                                        int T, int C, int pitch, int NS, int tw2_shift, int tw4_shift, int c,
+                                        int j, bool valid, bool first, bool last, int sw,
+                                        int64_t in_e, int64_t out_e, int64_t line, float scale) {
   // The shape arguments arrive in VGPRs (this is a call); they are the same in
   // every lane, so move them to SGPRs: the divisions and branches on them then
   // run once per wave on the scalar unit instead of on the VALU.
@@ -107,13 +183,14 @@ __device__ __noinline__ void mixed_pass(const gcf *__restrict__ src, gcf *__rest
   tw4_shift = __builtin_amdgcn_readfirstlane(tw4_shift);
   first = __builtin_amdgcn_readfirstlane((int)first) != 0;
   last = __builtin_amdgcn_readfirstlane((int)last) != 0;
+  sw = __builtin_amdgcn_readfirstlane(sw);
   // element strides and in-line offsets fit 32 bits (checked by the planner:
   // (L - 1) * stride < 2^31), so the per-element index math stays 32-bit
   const uint32_t ie = (uint32_t)__builtin_amdgcn_readfirstlane((int)in_e);
   const uint32_t oe = (uint32_t)__builtin_amdgcn_readfirstlane((int)out_e);
   scale = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(scale)));
   const int M = L / R;
-  constexpr int QM = (16 + R - 1) / R;  // butterflies per thread (T >= L/16)
+  constexpr int QM = mixed_qmax(R);  // butterflies per thread
   auto li = [&](int m, int pos) {
     return m == ELEM_FAST ? midx_elem(pitch, c, pos) : midx_line(C, c, pos);
   };
@@ -138,6 +215,10 @@ __device__ __noinline__ void mixed_pass(const gcf *__restrict__ src, gcf *__rest
       if (k >= NS) k -= NS;
     }
   }
+  FourStepTw<R, QM> f4;
+  if (TW4 && last)
+    f4.load(tw4_lo, tw4_hi, tw4_shift, valid ? (uint32_t)line : 0u, (uint32_t)j, (uint32_t)T,
+            (uint32_t)M);
   if (first) {
     ntw = __builtin_amdgcn_readfirstlane(ntw);
     const int tid = (int)threadIdx.x;
@@ -161,7 +242,7 @@ __device__ __noinline__ void mixed_pass(const gcf *__restrict__ src, gcf *__rest
 #pragma unroll
   for (int q = 0; q < QM; ++q) {
     if (!act[q]) continue;
-    if ((SW & 1) && first) {
+    if ((sw & 1) && first) {
 #pragma unroll
       for (int r = 0; r < R; ++r) v[q][r] = cswap(v[q][r]);
     }
@@ -170,6 +251,13 @@ __device__ __noinline__ void mixed_pass(const gcf *__restrict__ src, gcf *__rest
       apply_pass_twiddles<R>(v[q], tw2, tw2_shift, (uint32_t)kq[q] * step);
     }
     Dft<R>::run(v[q]);
+    if (TW4 && last) {
+      f4.apply(v[q], q, tw4_tab + c, C);  // the last pass's outputs are k1 = b + r*NS
+    }
+    if ((sw & 2) && last) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) v[q][r] = cswap(cscale(v[q][r], scale));
+    }
   }
   if (!first) __syncthreads();  // every read of this pass precedes the in-place writes
 #pragma unroll
@@ -178,46 +266,54 @@ __device__ __noinline__ void mixed_pass(const gcf *__restrict__ src, gcf *__rest
     const int b = j + T * q;
     const int k = kq[q];
     const int base = (b - k) * R + k;
-    // Four-step twiddles of the last pass: its outputs are k1 = b + r*NS, so
-    // w_N^{line k1} = A * B^r with A = w_N^{line b}, B = w_N^{line NS} (two
-    // table lookups per butterfly) and B^r from a product tree of depth <= 4.
-    cf tw[R];
-    if (TW4 && last) {
-      const uint32_t msk = (1u << tw4_shift) - 1u;
-      const uint32_t ea = (uint32_t)line * (uint32_t)b, eb = (uint32_t)line * (uint32_t)NS;
-      const cf A = cmul(ldc(tw4_hi, ea >> tw4_shift), ldc(tw4_lo, ea & msk));
-      const cf B = cmul(ldc(tw4_hi, eb >> tw4_shift), ldc(tw4_lo, eb & msk));
-      cf Bp[R];
-      Bp[0] = make_float2(1.0f, 0.0f);
-      if constexpr (R > 1) Bp[1] = B;
+    if (TW4 == TW4_STREAM && last) {
+      // the four-step intermediate, streamed: it leaves the L2 to the lines the
+      // tile's neighbours read (the four-step signals of the ragged batch: 583
+      // us plain, 554 streamed)
 #pragma unroll
-      for (int r = 2; r < R; ++r) {
-        int p2 = 1;
-        while (2 * p2 <= r) p2 *= 2;
-        Bp[r] = (r == p2) ? cmul(Bp[p2 / 2], Bp[p2 / 2]) : cmul(Bp[p2], Bp[r - p2]);
-      }
-      tw[0] = A;
+      for (int r = 0; r < R; ++r) stc_nt(dst, (uint32_t)(base + r * NS) * oe, v[q][r]);
+    } else if (last && OMAP == MAP) {
 #pragma unroll
-      for (int r = 1; r < R; ++r) tw[r] = cmul(A, Bp[r]);
-    }
+      for (int r = 0; r < R; ++r) stc(dst, (uint32_t)(base + r * NS) * oe, v[q][r]);
+    } else if (last) {
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int pos = base + r * NS;
-      cf y = v[q][r];
-      if (last) {
-        if (TW4) y = cmul(y, tw[r]);
-        if (SW & 2) y = cswap(cscale(y, scale));
-        if (OMAP == MAP) {
-          stc(dst, (uint32_t)pos * oe, y);
-          continue;
-        }
-        stc(lds, li(OMAP, pos), y);
-      } else {
-        stc(lds, li(MAP, pos), y);
-      }
+      for (int r = 0; r < R; ++r) stc(lds, li(OMAP, base + r * NS), v[q][r]);
+    } else {
+#pragma unroll
+      for (int r = 0; r < R; ++r) stc(lds, li(MAP, base + r * NS), v[q][r]);
     }
   }
   if (!last || OMAP != MAP) __syncthreads();
+}
+
+// The pass of run-time radix R.
+template <int MAP, int OMAP, int TW4, class... A>
+__device__ __forceinline__ void mixed_pass_any(int R, A... args) {
+#define PASS(RR) \
+  case RR:       \
+    mixed_pass<MAP, OMAP, TW4, RR>(args...); \
+    break
+  switch (R) {
+    PASS(2);
+    PASS(3);
+    PASS(4);
+    PASS(5);
+    PASS(6);
+    PASS(7);
+    PASS(8);
+    PASS(9);
+    PASS(10);
+    PASS(12);
+    PASS(14);
+    PASS(15);
+    PASS(16);
+    PASS(18);
+    PASS(20);
+    PASS(21);
+    PASS(24);
+    PASS(25);
+  }
+#undef PASS
 }
 
 // One tile (up to C lines of length L) through every pass.  Thread (c, j)
@@ -227,7 +323,7 @@ __device__ __noinline__ void mixed_pass(const gcf *__restrict__ src, gcf *__rest
 struct TileLine {
   const cf *src;
   cf *dst;
-  int64_t in_e, out_e, line;
+  int64_t in_e, out_e, line, line0;  // line0: the tile's first line
   int c, j;
   bool valid;
   cf *dst2;      // staged store: output base of line c2
@@ -243,6 +339,7 @@ struct LineShape {
   int tw4_shift;
   float scale;
   int tw_lds;     // LDS element offset of the copied table (after the tile data)
+  int64_t lines;  // four-step: lines of the matrix
 };
 
 // entries of the two-level table of w_L: 2^s lo entries and ceil(L / 2^s) hi
@@ -250,7 +347,7 @@ __host__ __device__ inline int tw2_entries(int L, int shift) {
   return (1 << shift) + (L + (1 << shift) - 1) / (1 << shift);
 }
 
-template <int MAP, int OMAP, bool TW4, int SW>
+template <int MAP, int OMAP, int TW4, int SW>
 __device__ __forceinline__ void mixed_tile(const LineShape &sh, const TileLine &t, cf *lds,
                                            int nthreads) {
   if (sh.P == 0) {  // length 1: the transform is the identity, up to the swaps and the scale
@@ -269,27 +366,24 @@ __device__ __forceinline__ void mixed_tile(const LineShape &sh, const TileLine &
   const int ntw = tw2_entries(sh.L, sh.tw2_shift);
   for (int i = threadIdx.x + nthreads; i < ntw; i += nthreads) stc(twl, i, sh.tw2[i]);
   const int ntw0 = ntw < nthreads ? ntw : nthreads;
+  if constexpr (TW4) {
+    // published by the barrier that ends the first pass (a one-pass line has
+    // none, and its own)
+    const int RL = (int)((sh.codes >> (5 * (sh.P - 1))) & 31u);
+    four_step_fill(twl + ntw, as_glb(sh.tw4_lo), as_glb(sh.tw4_hi), sh.tw4_shift, sh.C,
+                   (uint32_t)t.line0, (uint32_t)sh.lines, (uint32_t)sh.L, (uint32_t)(sh.L / RL),
+                   (uint32_t)sh.T, (int)threadIdx.x, nthreads);
+    if (sh.P == 1) __syncthreads();
+  }
   int ns = 1;
   for (int p = 0; p < sh.P; ++p) {
     const bool first = p == 0, last = p == sh.P - 1;
     const int R = (int)((sh.codes >> (5 * p)) & 31u);
-#define PASS(RR)                                                                                 \
-  mixed_pass<MAP, OMAP, TW4, SW, RR>(as_glb(t.src), as_glb(t.dst), as_lds(lds), twl,            \
-                                     as_glb(sh.tw2), ntw0,                                       \
-                                     as_glb(sh.tw4_lo), as_glb(sh.tw4_hi), sh.L, sh.T, sh.C,      \
-                                     sh.pitch, ns, sh.tw2_shift, sh.tw4_shift, t.c, t.j, t.valid, \
-                                     first, last, t.in_e, t.out_e, t.line, sh.scale)
-    switch (R) {
-      case 2: PASS(2); break;
-      case 3: PASS(3); break;
-      case 4: PASS(4); break;
-      case 5: PASS(5); break;
-      case 7: PASS(7); break;
-      case 9: PASS(9); break;
-      case 8: PASS(8); break;
-      default: PASS(16); break;
-    }
-#undef PASS
+    mixed_pass_any<MAP, OMAP, TW4>(R, as_glb(t.src), as_glb(t.dst), as_lds(lds), twl,
+                                   as_glb(sh.tw2), ntw0, as_glb(sh.tw4_lo), as_glb(sh.tw4_hi),
+                                   twl + ntw, sh.L, sh.T, sh.C, sh.pitch, ns, sh.tw2_shift, sh.tw4_shift, t.c,
+                                   t.j, t.valid, first, last, SW, t.in_e, t.out_e, t.line,
+                                   sh.scale);
     ns *= R;
   }
   if (OMAP != MAP && t.valid2) {

@@ -9,11 +9,16 @@
 // (the last pass to HBM), in place, with a barrier between the reads and the
 // writes.  Pass twiddles w_{Ns R}^{k r} = w_L^{k r L/(Ns R)} are rebuilt from a
 // two-level table of w_L made in FP64 on the host.
+#include <string>
+
 #include "mixed_device.h"
 
 namespace dpfft {
 
-template <int MAP, int OMAP, bool TW4, int SW>
+// longest line a workgroup transforms
+constexpr int64_t kMixedMaxLine = 16384;
+
+template <int MAP, int OMAP, int TW4, int SW>
 __global__ void __launch_bounds__(1024) k_mixed(const cf *__restrict__ in, cf *__restrict__ out,
                                                 MixedArgs a) {
   extern __shared__ cf lds[];
@@ -23,10 +28,11 @@ __global__ void __launch_bounds__(1024) k_mixed(const cf *__restrict__ in, cf *_
   const int64_t bb = tile / a.tiles_per_batch;
   const int64_t line0 = (int64_t)(tile - bb * a.tiles_per_batch) * mp.C;
   LineShape sh{mp.L, mp.T, mp.C, mp.pitch, mp.P, mp.tw2_shift, mp.codes, a.tw2,
-               a.tw4_lo, a.tw4_hi, a.tw4_shift, a.scale, mp.tw_lds};
+               a.tw4_lo, a.tw4_hi, a.tw4_shift, a.scale, mp.tw_lds, a.lines};
   TileLine t;
   t.c = MAP == ELEM_FAST ? tid / mp.T : tid % mp.C;
   t.j = MAP == ELEM_FAST ? tid % mp.T : tid / mp.C;
+  t.line0 = line0;
   t.line = line0 + t.c;
   t.valid = tid < mp.C * mp.T && t.line < a.lines;
   t.src = in + bb * a.in_b + t.line * a.in_l;
@@ -43,57 +49,54 @@ __global__ void __launch_bounds__(1024) k_mixed(const cf *__restrict__ in, cf *_
 // ---------------------------------------------------------------------------
 // host helpers
 // ---------------------------------------------------------------------------
-bool mixed_radices(int64_t L, MixedPlan *mp, int order) {
-  int64_t n = L;
-  int np = 0;
-  int cnt[17] = {};
-  for (int p : {2, 3, 5, 7})
-    while (n % p == 0) {
-      n /= p;
-      cnt[p]++;
-    }
-  if (n != 1) return false;
-  auto push = [&](int r) {
-    if (np >= kMaxPasses) return false;
-    mp->radix[np++] = r;
-    return true;
-  };
-  auto push_odd = [&]() {
-    for (int p : {7, 5})
-      for (int i = 0; i < cnt[p]; ++i)
-        if (!push(p)) return false;
-    // pairs of 3s as radix-9 passes (3 x 3 in registers): one LDS exchange
-    // fewer per pair
-    for (int i = 0; i < cnt[3] / 2; ++i)
-      if (!push(9)) return false;
-    if (cnt[3] % 2 && !push(3)) return false;
-    return true;
-  };
-  if (order == 1 && !push_odd()) return false;
-  int twos = cnt[2];
-  while (twos >= 4) {
-    if (!push(16)) return false;
-    twos -= 4;
+bool mixed_radices(int64_t L, MixedPlan *mp, int order, int tmax) {
+  if (L < 1 || L > kMixedMaxLine) return false;
+  for (int64_t n = L; n > 1;) {
+    const int p = n % 2 == 0 ? 2 : n % 3 == 0 ? 3 : n % 5 == 0 ? 5 : n % 7 == 0 ? 7 : 0;
+    if (!p) return false;
+    n /= p;
   }
-  if (twos == 3 && !push(8)) return false;
-  if (twos == 2 && !push(4)) return false;
-  if (twos == 1 && !push(2)) return false;
-  if (order != 1 && !push_odd()) return false;
+  const RadixPlan r = radix_plan((int)L, order, tmax);
+  if (r.T == 0) return false;
   mp->L = (int32_t)L;
-  mp->P = np;
+  mp->P = r.P;
+  mp->T = r.T;
   int ns = 1;
   mp->codes = 0;
-  for (int p = 0; p < np; ++p) {
+  for (int p = 0; p < r.P; ++p) {
+    mp->radix[p] = r.R[p];
     mp->ns[p] = ns;
-    ns *= mp->radix[p];
-    mp->codes |= (uint64_t)mp->radix[p] << (5 * p);
+    ns *= r.R[p];
+    mp->codes |= (uint64_t)r.R[p] << (5 * p);
   }
-  mp->T = (int32_t)((L + 15) / 16);
   int lg = 0;
   while ((int64_t(1) << lg) < L) ++lg;
   mp->tw2_shift = (lg + 1) / 2;
   mp->pitch = (int32_t)(L + (L >> 4) + 1);
   return true;
+}
+
+bool mixed_covers(const MixedPlan &mp) {
+  for (int p = 0; p < mp.P; ++p)
+    if (mp.L / mp.radix[p] > mp.T * mixed_qmax(mp.radix[p])) return false;
+  return true;
+}
+
+std::string mixed_factors(int64_t L) {
+  int cnt[8] = {};
+  for (int p : {2, 3, 5, 7})
+    for (; L % p == 0; L /= p) ++cnt[p];
+  std::string s;
+  auto push = [&](int r, int times) {
+    for (int i = 0; i < times; ++i) s += (s.empty() ? "" : "x") + std::to_string(r);
+  };
+  push(16, cnt[2] / 4);
+  if (cnt[2] % 4) push(1 << (cnt[2] % 4), 1);
+  push(7, cnt[7]);
+  push(5, cnt[5]);
+  push(9, cnt[3] / 2);
+  push(3, cnt[3] % 2);
+  return s;
 }
 
 int mixed_tile_elems(const MixedPlan &mp, int map, int omap) {
@@ -107,26 +110,29 @@ int mixed_tile_elems(const MixedPlan &mp, int map, int omap) {
   return (int)n;
 }
 
-int mixed_lds_bytes(const MixedPlan &mp, int map, int omap) {
-  return (mixed_tile_elems(mp, map, omap) + tw2_entries(mp.L, mp.tw2_shift)) * (int)sizeof(cf);
+int mixed_lds_bytes(const MixedPlan &mp, int map, int omap, bool tw4) {
+  return (mixed_tile_elems(mp, map, omap) + tw2_entries(mp.L, mp.tw2_shift) +
+          (tw4 ? kFourStepVals * mp.C : 0)) * (int)sizeof(cf);
 }
 
-const void *mixed_kernel(int map, int omap, bool tw4, int sw) {
+const void *mixed_kernel(int map, int omap, int tw4, int sw) {
 #define MK(M, O, TW, S) \
   if (map == M && omap == O && tw4 == TW && sw == S) return (const void *)&k_mixed<M, O, TW, S>;
   // single-pass rows: forward, inverse (swap in+out), 2D row pass inverse (swap in)
-  MK(ELEM_FAST, ELEM_FAST, false, 0)
-  MK(ELEM_FAST, ELEM_FAST, false, 1)
-  MK(ELEM_FAST, ELEM_FAST, false, 3)
+  MK(ELEM_FAST, ELEM_FAST, TW4_NONE, 0)
+  MK(ELEM_FAST, ELEM_FAST, TW4_NONE, 1)
+  MK(ELEM_FAST, ELEM_FAST, TW4_NONE, 3)
   // column tiles: 2D column pass (fwd, inv = swap out), four-step first pass (fwd, swap in)
-  MK(LINE_FAST, LINE_FAST, false, 0)
-  MK(LINE_FAST, LINE_FAST, false, 2)
-  MK(LINE_FAST, LINE_FAST, false, 3)
-  MK(LINE_FAST, LINE_FAST, true, 0)
-  MK(LINE_FAST, LINE_FAST, true, 1)
+  MK(LINE_FAST, LINE_FAST, TW4_NONE, 0)
+  MK(LINE_FAST, LINE_FAST, TW4_NONE, 2)
+  MK(LINE_FAST, LINE_FAST, TW4_NONE, 3)
+  MK(LINE_FAST, LINE_FAST, TW4_PLAIN, 0)
+  MK(LINE_FAST, LINE_FAST, TW4_PLAIN, 1)
+  MK(LINE_FAST, LINE_FAST, TW4_STREAM, 0)
+  MK(LINE_FAST, LINE_FAST, TW4_STREAM, 1)
   // four-step second pass: rows stored transposed (fwd, swap out)
-  MK(ELEM_FAST, LINE_FAST, false, 0)
-  MK(ELEM_FAST, LINE_FAST, false, 2)
+  MK(ELEM_FAST, LINE_FAST, TW4_NONE, 0)
+  MK(ELEM_FAST, LINE_FAST, TW4_NONE, 2)
 #undef MK
   return nullptr;
 }

@@ -13,7 +13,7 @@ namespace dpfft {
 //               element offsets of the signals are sigoff[off .. off + C)
 //   RK_COLUMNS: columns [first, first + C) of a four-step signal at element
 //               offset `off` (n1-point column FFTs and the twiddle w_N^{n2 k1},
-//               into the workspace at ws_off)
+//               into the workspace at ws_off, rows wp elements apart)
 //   RK_ROWS   : rows [first, first + C) of that signal (n2-point FFTs, stored
 //               transposed into the output); runs in the second launch, after
 //               every column item
@@ -26,7 +26,7 @@ struct RaggedItem {
   int32_t tw4_shift;
   int32_t ct;          // 1: the line length has compile-time instances (tw2_off then
                        // names its per-pass twiddle table instead of the two-level one)
-  int32_t pad;
+  int32_t wp;          // workspace elements between the rows of the four-step intermediate
   uint64_t codes;      // radices, 5 bits each
   int64_t tw2_off;     // two-level pass table of w_L in the table buffer
   int64_t off;         // RK_SINGLE: first index into sigoff; else: the signal's element offset

@@ -31,7 +31,7 @@ __device__ __forceinline__ void ragged_item(const cf *__restrict__ in, cf *__res
                                             const RaggedArgs &a, const RaggedItem &d, cf *lds) {
   const int tid = threadIdx.x;
   LineShape sh{d.L, d.T, d.C, d.pitch, d.P, d.tw2_shift, d.codes, a.tables + d.tw2_off,
-               nullptr, nullptr, 0, 1.0f, d.tw_lds};
+               nullptr, nullptr, 0, 1.0f, d.tw_lds, d.n2};
   TileLine t;
   const bool in_tile = tid < d.C * d.T;
 
@@ -46,7 +46,7 @@ __device__ __forceinline__ void ragged_item(const cf *__restrict__ in, cf *__res
     t.line = 0;
     t.valid2 = false;
     sh.scale = 1.0f / (float)d.L;
-    mixed_tile<ELEM_FAST, ELEM_FAST, false, INV ? 3 : 0>(sh, t, lds, NTH);
+    mixed_tile<ELEM_FAST, ELEM_FAST, TW4_NONE, INV ? 3 : 0>(sh, t, lds, NTH);
   } else if (d.kind == RK_COLUMNS) {
     if constexpr (NTH == kRaggedThreads) {
       if (d.ct) {
@@ -58,7 +58,8 @@ __device__ __forceinline__ void ragged_item(const cf *__restrict__ in, cf *__res
         const int64_t n2 = d.first + ca.c;
         ca.src = as_glb(in + d.off + n2);
         ca.dst = as_glb(a.ws + d.ws_off + n2);
-        ca.in_e = ca.out_e = (uint32_t)d.n2;
+        ca.in_e = (uint32_t)d.n2;
+        ca.out_e = (uint32_t)d.wp;
         ca.line = (uint32_t)n2;
         ca.tw4_lo = as_glb(a.tables + d.tw4_lo_off);
         ca.tw4_hi = as_glb(a.tables + d.tw4_hi_off);
@@ -87,10 +88,12 @@ __device__ __forceinline__ void ragged_item(const cf *__restrict__ in, cf *__res
     const int64_t n2 = d.first + t.c;
     t.src = in + d.off + n2;
     t.dst = a.ws + d.ws_off + n2;
-    t.in_e = t.out_e = d.n2;
+    t.in_e = d.n2;
+    t.out_e = d.wp;
     t.line = n2;
+    t.line0 = d.first;
     t.valid2 = false;
-    mixed_tile<LINE_FAST, LINE_FAST, true, INV ? 1 : 0>(sh, t, lds, NTH);
+    mixed_tile<LINE_FAST, LINE_FAST, TW4_STREAM, INV ? 1 : 0>(sh, t, lds, NTH);
   } else {
     if constexpr (NTH == kRaggedThreads) {
       if (d.ct) {
@@ -100,7 +103,7 @@ __device__ __forceinline__ void ragged_item(const cf *__restrict__ in, cf *__res
         ca.j = tid % d.T;
         ca.valid = in_tile;
         const int64_t k1 = d.first + ca.c;
-        ca.src = as_glb(a.ws + d.ws_off + k1 * d.n2);
+        ca.src = as_glb(a.ws + d.ws_off + k1 * d.wp);
         ca.in_e = 1;
         ca.out_e = (uint32_t)d.n1;
         ca.line = (uint32_t)k1;
@@ -127,7 +130,7 @@ __device__ __forceinline__ void ragged_item(const cf *__restrict__ in, cf *__res
     t.j = tid % d.T;
     t.valid = in_tile;
     const int64_t k1 = d.first + t.c;
-    t.src = a.ws + d.ws_off + k1 * d.n2;
+    t.src = a.ws + d.ws_off + k1 * d.wp;
     t.dst = nullptr;
     t.in_e = 1;
     t.out_e = d.n1;
@@ -137,7 +140,7 @@ __device__ __forceinline__ void ragged_item(const cf *__restrict__ in, cf *__res
     t.valid2 = in_tile;
     t.dst2 = out + d.off + d.first + t.c2;
     sh.scale = (float)(1.0 / ((double)d.n1 * (double)d.n2));
-    mixed_tile<ELEM_FAST, LINE_FAST, false, INV ? 2 : 0>(sh, t, lds, NTH);
+    mixed_tile<ELEM_FAST, LINE_FAST, TW4_NONE, INV ? 2 : 0>(sh, t, lds, NTH);
   }
 }
 

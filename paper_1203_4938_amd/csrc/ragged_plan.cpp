@@ -283,13 +283,26 @@ int64_t tw_elems(const MixedPlan &mp) {
 constexpr int64_t kBudget = kRaggedLdsBytes / (int64_t)sizeof(float2);
 constexpr int64_t kBigBudget = kRaggedBigLdsBytes / (int64_t)sizeof(float2);
 
-// the lengths one 256-thread ragged workgroup transforms in a single pass
-bool fits_single(const MixedPlan &mp) {
-  return mp.T <= kRaggedThreads && tile_lds(mp, 1, ELEM_FAST) + tw_elems(mp) <= kBudget;
+int64_t align16(int64_t v) { return (v + 15) & ~int64_t(15); }
+
+// A 7-smooth line of L points in LDS: the tile, then the two-level table
+// (tile_lds + tw_elems of any radix plan of L).
+int64_t line_elems(int64_t L) {
+  int s = 0;
+  while ((int64_t(1) << s) < L) ++s;
+  s = (s + 1) / 2;
+  return L + (L >> 4) + 1 + (int64_t(1) << s) + ((L + (int64_t(1) << s) - 1) >> s);
 }
+// the lengths one 256-thread ragged workgroup transforms in a single pass (16
+// points per thread always have a radix plan)
+bool fits_single(int64_t L) { return L <= 16 * kRaggedThreads && line_elems(L) <= kBudget; }
 // ... and one 1024-thread workgroup
-bool fits_big(const MixedPlan &mp) {
-  return mp.T <= kRaggedBigThreads && tile_lds(mp, 1, ELEM_FAST) + tw_elems(mp) <= kBigBudget;
+bool fits_big(int64_t L) { return L <= 16 * kRaggedBigThreads && line_elems(L) <= kBigBudget; }
+
+// radix plan of a line: lines that fit a 256-thread workgroup take at most
+// its threads
+bool ragged_radices(int64_t L, MixedPlan *mp, int order) {
+  return mixed_radices(L, mp, order, fits_single(L) ? kRaggedThreads : kRaggedBigThreads);
 }
 
 }  // namespace
@@ -302,7 +315,7 @@ std::string dpfft::ragged_tune_key(int64_t L) {
   // the ragged kernels' shape constants and the version of the choice format
   uint64_t h = 1469598103934665603ull;
   for (int64_t v : {(int64_t)kRaggedThreads, (int64_t)kRaggedLdsBytes, (int64_t)kRaggedBigThreads,
-                    (int64_t)kRaggedBigLdsBytes, (int64_t)sizeof(RaggedItem), (int64_t)2}) {
+                    (int64_t)kRaggedBigLdsBytes, (int64_t)sizeof(RaggedItem), (int64_t)3}) {
     for (int b = 0; b < 8; ++b) {
       h ^= (uint64_t)((v >> (8 * b)) & 0xff);
       h *= 1099511628211ull;
@@ -315,13 +328,11 @@ std::string dpfft::ragged_tune_key(int64_t L) {
 
 // Column lengths n1 of the four-step splits of L whose two factors both fit
 // one 256-thread ragged workgroup, nearest to sqrt(L) first (at most `max`).
-static std::vector<int64_t> ragged_splits(int64_t L, int order, int max) {
+static std::vector<int64_t> ragged_splits(int64_t L, int max) {
   std::vector<std::pair<double, int64_t>> c;
   for (int64_t d = 2; d * 2 <= L; ++d) {
     if (L % d) continue;
-    MixedPlan a{}, b{};
-    if (!mixed_radices(d, &a, order) || !mixed_radices(L / d, &b, order)) continue;
-    if (!fits_single(a) || !fits_single(b)) continue;
+    if (!fits_single(d) || !fits_single(L / d)) continue;
     c.push_back({std::fabs(std::log((double)d) - 0.5 * std::log((double)L)), d});
   }
   std::stable_sort(c.begin(), c.end());
@@ -335,12 +346,10 @@ static std::vector<int64_t> ragged_splits(int64_t L, int order, int max) {
 
 // Forms of a ragged length that a choice may name: single pass in a 256- or
 // a 1024-thread workgroup, four-step.
-static bool ragged_form_fits(int64_t L, int order, int form) {
-  MixedPlan mp{};
-  if (!mixed_radices(L, &mp, order)) return false;
-  if (form == 0) return fits_single(mp);
-  if (form == 2) return fits_big(mp) && !fits_single(mp);
-  return !ragged_splits(L, order, 1).empty();
+static bool ragged_form_fits(int64_t L, int form) {
+  if (form == 0) return fits_single(L);
+  if (form == 2) return fits_big(L) && !fits_single(L);
+  return !ragged_splits(L, 1).empty();
 }
 
 // Choices worth timing for one ragged length: each radix order (the second
@@ -351,13 +360,16 @@ std::vector<std::string> dpfft::ragged_candidates(int64_t L) {
   uint64_t codes0 = 0;
   for (int order : {0, 1}) {
     MixedPlan mp{};
-    if (!mixed_radices(L, &mp, order)) continue;
-    if (order == 0) codes0 = mp.codes;
-    else if (mp.codes == codes0) continue;
+    if (fits_big(L)) {
+      if (!ragged_radices(L, &mp, order)) continue;
+      if (order == 0) codes0 = mp.codes;
+    }
     const std::string o = "o=" + std::to_string(order);
-    if (ragged_form_fits(L, order, 0)) out.push_back(o + " f=0");
-    if (ragged_form_fits(L, order, 2)) out.push_back(o + " f=2");
-    for (int64_t n1 : ragged_splits(L, order, 3))
+    const bool same = order == 1 && fits_big(L) && mp.codes == codes0;
+    if (same) continue;
+    if (ragged_form_fits(L, 0)) out.push_back(o + " f=0");
+    if (ragged_form_fits(L, 2)) out.push_back(o + " f=2");
+    for (int64_t n1 : ragged_splits(L, 3))
       out.push_back(o + " f=1 s=" + std::to_string(n1));
   }
   return out;
@@ -406,7 +418,7 @@ fft_status_t plan_ragged(dpfft_plan_s *P, const int64_t *sizes, const int64_t *o
     auto it = lines.find({L, order});
     if (it != lines.end()) return &it->second;
     MixedPlan mp{};
-    if (!mixed_radices(L, &mp, order)) return nullptr;
+    if (!ragged_radices(L, &mp, order)) return nullptr;
     std::vector<std::complex<double>> lo, hi;
     fourstep_tables(L, mp.tw2_shift, lo, hi);
     lo.insert(lo.end(), hi.begin(), hi.end());
@@ -459,27 +471,54 @@ fft_status_t plan_ragged(dpfft_plan_s *P, const int64_t *sizes, const int64_t *o
   int nbig_sizes = 0, nsingle_sizes = 0, nlarge_sizes = 0, ntuned = 0;
   auto lg = [](int64_t L) { return std::max(1.0, std::log2((double)L)); };
 
+  // per-length choices: the tuner's candidate, a forced plan, the tuning
+  // cache, else the heuristic (256-thread single pass where it fits, then the
+  // 1024-thread single pass, then the four-step with the split nearest sqrt(L))
+  struct Choice {
+    Override ov;
+    int form;
+    int64_t n1;  // four-step: column length (the named one where it fits)
+  };
+  std::map<int64_t, Choice> choices;
+  int64_t ws_dense = 0, ws_aligned = 0;
+  for (const auto &kv : by_size) {
+    const int64_t L = kv.first;
+    Choice c{read_ragged_override(L), 0, 0};
+    c.form = c.ov.form;
+    if (c.form < 0 || !ragged_form_fits(L, c.form))
+      c.form = fits_single(L) ? 0 : (c.ov.big != 0 && fits_big(L)) ? 2 : 1;
+    if (!ragged_form_fits(L, c.form))
+      return fail(FFT_E_UNSUPPORTED, "ragged size " + std::to_string(L) + " fits no form");
+    if (c.form == 1) {
+      c.n1 = ragged_splits(L, 1)[0];
+      if (c.ov.split > 0)
+        for (int64_t d : ragged_splits(L, 64))
+          if (d == c.ov.split) c.n1 = d;
+      ws_dense += L * (int64_t)kv.second.size();
+      ws_aligned += align16(L / c.n1) * c.n1 * (int64_t)kv.second.size();
+    }
+    choices[L] = c;
+  }
+  // Rows of the intermediates on whole 128-byte lines, so that the column
+  // tiles write and the row tiles read whole lines: the 10,000-signal batch
+  // 784 us dense, 741 so.  A batch whose dense workspace fits the library's own
+  // scratch array keeps fitting it.
+  const int64_t scratch = kScratchBytes / (int64_t)sizeof(float2);
+  const bool align_rows = ws_aligned <= scratch || ws_dense > scratch;
+
   for (const auto &kv : by_size) {
     const int64_t L = kv.first;
     const auto &sigs = kv.second;
-    // per-length choices: the tuner's candidate, a forced plan, the tuning
-    // cache, else the heuristic (256-thread single pass where it fits, then
-    // the 1024-thread single pass, then the four-step with the split nearest
-    // sqrt(L))
-    const Override ov = read_ragged_override(L);
+    const Choice &ch = choices[L];
+    const Override &ov = ch.ov;
     if (!ov.empty()) ++ntuned;
     const int order = ov.order >= 0 ? ov.order : 0;
-    MixedPlan probe{};
-    if (!mixed_radices(L, &probe, order))
-      return fail(FFT_E_UNSUPPORTED, "no radix plan for ragged size " + std::to_string(L));
-    int form = ov.form;
-    if (form < 0 || !ragged_form_fits(L, order, form))
-      form = fits_single(probe) ? 0 : (ov.big != 0 && fits_big(probe)) ? 2 : 1;
-    if (!ragged_form_fits(L, order, form))
-      return fail(FFT_E_UNSUPPORTED, "ragged size " + std::to_string(L) + " fits no form");
+    const int form = ch.form;
     if (form == 0 || form == 2) {
       const bool big = form == 2;
-      const LineInfo &li = *line_of(L, order);
+      const LineInfo *lp = line_of(L, order);
+      if (!lp) return fail(FFT_E_UNSUPPORTED, "no radix plan for ragged size " + std::to_string(L));
+      const LineInfo &li = *lp;
       const MixedPlan &mp = li.mp;
       const int nth = big ? kRaggedBigThreads : kRaggedThreads;
       const int64_t budget = big ? kBigBudget : kBudget;
@@ -503,21 +542,21 @@ fft_status_t plan_ragged(dpfft_plan_s *P, const int64_t *sizes, const int64_t *o
       continue;
     }
     // four-step: L = n1 * n2
-    // the named split where it fits this length, else the one nearest sqrt(L)
-    int64_t n1 = ragged_splits(L, order, 1)[0];
-    if (ov.split > 0)
-      for (int64_t d : ragged_splits(L, order, 64))
-        if (d == ov.split) n1 = d;
-    const int64_t n2 = L / n1;
+    const int64_t n1 = ch.n1, n2 = L / n1, wp = align_rows ? align16(n2) : n2;
     const LineInfo *l1 = line_of(n1, order), *l2 = line_of(n2, order);
     if (!l1 || !l2) return fail(FFT_E_UNSUPPORTED, "no radix plan for ragged size " + std::to_string(L));
     const MixedPlan &m1 = l1->mp, &m2 = l2->mp;
     int CA = std::max(1, kRaggedThreads / m1.T), CB = std::max(1, kRaggedThreads / m2.T);
     if (ov.c[0] > 0) CA = std::min(CA, ov.c[0]);
     if (ov.c[1] > 0) CB = std::min(CB, ov.c[1]);
-    while (CA > 1 && tile_lds(m1, CA, LINE_FAST) + twn(*l1, true) > kBudget) --CA;
+    auto cols_lds = [&](int c) { return tile_lds(m1, c, LINE_FAST) + twn(*l1, true) + kFourStepVals * c; };
+    while (CA > 1 && cols_lds(CA) > kBudget) --CA;
     auto rows_lds = [&](int c) { return std::max(tile_lds(m2, c, ELEM_FAST), tile_lds(m2, c, LINE_FAST)); };
     while (CB > 1 && rows_lds(CB) + twn(*l2, true) > kBudget) --CB;
+    // whole 128-byte pieces of the intermediate's rows and, where n1 allows,
+    // of the output's (the batch: 797 us with as many lines as fit, 741 so)
+    if (CA > 16) CA -= CA % 16;
+    if (CB > 16) CB -= CB % 16;
     std::vector<std::complex<double>> lo, hi;
     int lgL = 0;
     while ((int64_t(1) << lgL) < L) ++lgL;
@@ -528,6 +567,7 @@ fft_status_t plan_ragged(dpfft_plan_s *P, const int64_t *sizes, const int64_t *o
       it.first = (int32_t)f;
       it.n1 = (int32_t)n1;
       it.n2 = (int32_t)n2;
+      it.wp = (int32_t)wp;
       it.off = P->roffsets[s];
       it.ws_off = ws_off;
       it.tw4_lo_off = lo_off;
@@ -545,9 +585,9 @@ fft_status_t plan_ragged(dpfft_plan_s *P, const int64_t *sizes, const int64_t *o
         items.push_back(four(item_for(RK_COLUMNS, *l1, c, data), s, ws, f));
         isbig.push_back(0);
         cost.push_back((int64_t)(c * n1 * lg(n1)));
-        lds_need = std::max(lds_need, data + twn(*l1, true));
+        lds_need = std::max(lds_need, cols_lds(c));
       }
-      ws += L;
+      ws += n1 * wp;
     }
     st->ranges.push_back({first_cols, (int)items.size() - first_cols, false});
     const int first_rows = (int)items.size();

@@ -25,7 +25,7 @@
 
 namespace {
 
-constexpr size_t kScratchBytes = size_t(64) << 20;  // 64 MiB: 8 Mi complex64 points
+using dpfft::kScratchBytes;
 static __device__ __align__(256) char scratch[kScratchBytes];
 
 constexpr int kMaxDevices = 64;

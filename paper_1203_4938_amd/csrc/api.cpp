@@ -232,6 +232,51 @@ std::string MixedStep::describe() const {
   return o.str();
 }
 
+// ---- real rows on the runtime-radix passes ----
+void MixedRealStep::bind(const float2 *tables) {
+  a.tw2 = tables + tw2_off;
+  a.tw4_lo = tables + lo_off;
+  a.tw4_hi = tables + hi_off;
+}
+
+hipError_t MixedRealStep::launch(const ExecCtx &ctx) const {
+  const float2 *s = buf_c(ctx, src, 0);
+  float2 *d = buf_m(ctx, dst, 0);
+  MixedArgs args = a;
+  void *kargs[] = {(void *)&s, (void *)&d, (void *)&args};
+  return hipLaunchKernel(mixed_real_kernel(inv), grid, dim3(threads), kargs, (size_t)lds_bytes,
+                         ctx.stream);
+}
+
+void MixedRealStep::extent(int64_t &max_in, int64_t &max_out, int &src_id, int &dst_id) const {
+  // the spectrum side holds L + 1 elements per line, the real side L pairs
+  const int64_t nb = (int64_t)grid.x / a.tiles_per_batch;
+  max_in = (nb - 1) * a.in_b + (a.lines - 1) * a.in_l + (inv ? a.mp.L : a.mp.L - 1);
+  max_out = (nb - 1) * a.out_b + (a.lines - 1) * a.out_l + (inv ? a.mp.L - 1 : a.mp.L);
+  src_id = src;
+  dst_id = dst;
+}
+
+hipError_t MixedRealStep::prepare() const {
+  return hipFuncSetAttribute(mixed_real_kernel(inv), hipFuncAttributeMaxDynamicSharedMemorySize,
+                             kLdsBytes);
+}
+
+bool MixedRealStep::valid() const {
+  return threads > 0 && threads <= 1024 && threads == a.mp.C * a.mp.T && lds_bytes <= kLdsBytes &&
+         mixed_covers(a.mp) && a.lines <= a.tiles_per_batch * a.mp.C;
+}
+
+std::string MixedRealStep::describe() const {
+  std::ostringstream o;
+  o << name << ": N=" << 2 * a.mp.L << " L=" << a.mp.L << " radices=" << mixed_factors(a.mp.L)
+    << " passes=";
+  for (int p = 0; p < a.mp.P; ++p) o << (p ? "x" : "") << a.mp.radix[p];
+  o << " pairs in LDS C=" << a.mp.C << " threads=" << threads << " grid=" << grid.x
+    << " lds=" << lds_bytes << "B";
+  return o.str();
+}
+
 // ---- matrix-core steps ----
 void MfmaStep::bind(const float2 *tables) {
   a.amat = reinterpret_cast<const uint16_t *>(tables + amat_off);
@@ -1149,88 +1194,91 @@ fft_status_t plan_real_1d(dpfft_plan_s *P) {
   return FFT_OK;
 }
 
-// Real-input images: forward = real rows -> ny x (nx/2 + 1) bins in `out`,
-// then the column transforms in place on `out`; inverse = column transforms
-// of `in` into the workspace (scale 1/ny), then the complex-to-real rows from
-// the workspace into `out` (scale 1/nx).
-// Real-input images whose sides are not both powers of two: the rows of
-// nx/2 complex pairs through the runtime-radix single pass, the pairing of
-// bin k with nx/2 - k per row, then the runtime-radix column tiles over the
-// nx/2 + 1 columns.  Forward: rows input -> workspace, pairing workspace ->
-// output, columns in place on the output.  Inverse: columns input ->
-// workspace (scale 1/ny), pairing workspace -> output (rows of nx/2), rows in
-// place on the output (scale 1/nx).
+// Real rows of nx = 2L samples <-> L + 1 bins with the pairing in LDS,
+// `rows` per batch item; the real side is dense, the spectrum side has its
+// rows `pitch` elements apart.
+std::unique_ptr<MixedRealStep> make_mixed_real(dpfft_plan_s *P, const char *name, int64_t L,
+                                               bool inv, int64_t rows, int64_t pitch, int C,
+                                               size_t lo_off, size_t hi_off, int shift) {
+  auto m = make_mixed(P, name, L, ELEM_FAST, ELEM_FAST, false, C);
+  if (!m) return nullptr;
+  auto s = std::make_unique<MixedRealStep>();
+  s->a = m->a;
+  s->inv = inv;
+  s->threads = m->threads;
+  s->lds_bytes = m->lds_bytes;
+  s->tw2_off = m->tw2_off;
+  s->lo_off = lo_off;
+  s->hi_off = hi_off;
+  s->name = name;
+  s->a.tw4_shift = shift;
+  s->a.in_b = s->a.out_b = 0;
+  s->a.in_l = inv ? pitch : L;
+  s->a.out_l = inv ? L : pitch;
+  s->a.in_e = s->a.out_e = 1;
+  s->a.lines = rows;
+  s->a.tiles_per_batch = (rows + C - 1) / C;
+  s->grid = dim3((unsigned)s->a.tiles_per_batch);
+  s->a.scale = inv ? (float)(1.0 / (double)(2 * L)) : 1.0f;
+  return s;
+}
+
+// Real-input images whose sides are not both powers of two, on the
+// runtime-radix kernels: real rows (nx reals <-> nx/2 + 1 bins, paired in
+// LDS) and column tiles over the nx/2 + 1 columns, the intermediate in the
+// workspace.  Forward: rows input -> workspace, columns workspace -> output.
+// Inverse: columns input -> workspace (scale 1/ny), rows workspace -> output
+// (scale 1/nx).
 fft_status_t plan_real_2d_mixed(dpfft_plan_s *P) {
   const int64_t NY = P->ny, NX = P->nx, B = P->batch;
   const int64_t L = NX / 2, W = L + 1, R = B * NY;
   const Override ov = read_override();
+  const int64_t pitch = W;
   const int CR = mixed_c(ov, 0, mixed_row_lines(L), L, ELEM_FAST, ELEM_FAST);
   const int CC = mixed_c(ov, 1, mixed_col_lines(NY, LINE_FAST), NY, LINE_FAST, LINE_FAST);
-  std::unique_ptr<MixedStep> row[2], col[2];
-  for (int i = 0; i < 2; ++i) {
-    row[i] = CR ? make_mixed(P, i ? "real_core_rows_inverse" : "real_core_rows", L, ELEM_FAST,
-                             ELEM_FAST, false, CR)
-                : nullptr;
-    col[i] = CC ? make_mixed(P, i ? "columns_inverse" : "columns", NY, LINE_FAST, LINE_FAST, false, CC)
-                : nullptr;
-    if (!row[i] || !col[i])
-      return fail(FFT_E_UNSUPPORTED, "no runtime-radix kernels for this real-input image");
-    MixedStep &r = *row[i];
-    r.a.in_b = r.a.out_b = 0;
-    r.a.in_l = r.a.out_l = L;
-    r.a.in_e = r.a.out_e = 1;
-    r.a.lines = R;
-    r.a.tiles_per_batch = (R + r.a.mp.C - 1) / r.a.mp.C;
-    r.grid = dim3((unsigned)r.a.tiles_per_batch);
-    r.first = r.last = true;
-    r.inv_scale = (float)(1.0 / (double)NX);
-    MixedStep &c = *col[i];
-    c.a.in_b = c.a.out_b = NY * W;
-    c.a.in_l = c.a.out_l = 1;
-    c.a.in_e = c.a.out_e = W;
-    c.a.lines = W;
-    c.a.tiles_per_batch = (W + c.a.mp.C - 1) / c.a.mp.C;
-    c.a.flags = F_REMAP;
-    c.grid = dim3((unsigned)(B * c.a.tiles_per_batch));
-    c.first = c.last = true;
-    c.inv_scale = (float)(1.0 / (double)NY);
-  }
+  if (!CR || !CC) return fail(FFT_E_UNSUPPORTED, "no runtime-radix kernels for this real-input image");
   std::vector<std::complex<double>> lo, hi;
   const int shift = (ilog2(NX) + 1) / 2;
   fourstep_tables(NX, shift, lo, hi);
   const size_t lo_off = P->tables.add(lo), hi_off = P->tables.add(hi);
-  auto pair = [&](bool inv) {
-    auto r = std::make_unique<RealPairStep>();
-    r->inv = inv;
-    r->name = inv ? "real_pairs_inverse" : "real_pairs";
-    r->a.L = L;
-    r->a.batch = R;
-    r->a.in_b = inv ? W : L;
-    r->a.out_b = inv ? L : W;
-    r->a.shift = shift;
-    r->lo_off = lo_off;
-    r->hi_off = hi_off;
-    r->src = BUF_WS;
-    r->dst = BUF_OUT;
-    return r;
-  };
-  row[0]->src = BUF_IN;
-  row[0]->dst = BUF_WS;
-  col[0]->src = col[0]->dst = BUF_OUT;
-  col[1]->src = BUF_IN;
-  col[1]->dst = BUF_WS;
-  row[1]->src = row[1]->dst = BUF_OUT;
-  P->steps.push_back(std::move(row[0]));
-  P->steps.push_back(pair(false));
-  P->steps.push_back(std::move(col[0]));
-  P->isteps.push_back(std::move(col[1]));
-  P->isteps.push_back(pair(true));
-  P->isteps.push_back(std::move(row[1]));
-  P->ws_bytes = (size_t)B * (size_t)NY * (size_t)W * sizeof(float2);
-  P->variant = "real 2d runtime-radix rows + pairing + columns";
+  for (int i = 0; i < 2; ++i) {
+    auto r = make_mixed_real(P, i ? "real_rows_inverse" : "real_rows", L, i == 1, R, pitch, CR,
+                             lo_off, hi_off, shift);
+    auto c = make_mixed(P, i ? "columns_inverse" : "columns", NY, LINE_FAST, LINE_FAST, false, CC);
+    if (!r || !c)
+      return fail(FFT_E_UNSUPPORTED, "no runtime-radix kernels for this real-input image");
+    c->a.in_e = i ? W : pitch;
+    c->a.out_e = i ? pitch : W;
+    c->a.in_b = NY * c->a.in_e;
+    c->a.out_b = NY * c->a.out_e;
+    c->a.in_l = c->a.out_l = 1;
+    c->a.lines = W;
+    c->a.tiles_per_batch = (W + c->a.mp.C - 1) / c->a.mp.C;
+    c->a.flags = F_REMAP;
+    c->grid = dim3((unsigned)(B * c->a.tiles_per_batch));
+    c->first = c->last = true;
+    c->inv_scale = (float)(1.0 / (double)NY);
+    r->src = i ? BUF_WS : BUF_IN;
+    r->dst = i ? BUF_OUT : BUF_WS;
+    c->src = i ? BUF_IN : BUF_WS;
+    c->dst = i ? BUF_WS : BUF_OUT;
+    if (i == 0) {
+      P->steps.push_back(std::move(r));
+      P->steps.push_back(std::move(c));
+    } else {
+      P->isteps.push_back(std::move(c));
+      P->isteps.push_back(std::move(r));
+    }
+  }
+  P->ws_bytes = (size_t)B * (size_t)NY * (size_t)pitch * sizeof(float2);
+  P->variant = "real 2d runtime-radix rows + columns";
   return FFT_OK;
 }
 
+// Real-input images: forward = real rows -> ny x (nx/2 + 1) bins in `out`,
+// then the column transforms in place on `out`; inverse = column transforms
+// of `in` into the workspace (scale 1/ny), then the complex-to-real rows from
+// the workspace into `out` (scale 1/nx).
 fft_status_t plan_real_2d(dpfft_plan_s *P) {
   const int64_t NY = P->ny, NX = P->nx, B = P->batch;
   if (!is_pow2(NY) || !is_pow2(NX)) return plan_real_2d_mixed(P);

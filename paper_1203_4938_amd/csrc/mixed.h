@@ -61,6 +61,9 @@ enum : int { TW4_NONE = 0, TW4_PLAIN = 1, TW4_STREAM = 2 };
 // Host: the kernel instance for (map, omap, TW4_*, swap mode); nullptr if none.
 const void *mixed_kernel(int map, int omap, int tw4, int sw);
 
+// Host: the real-row kernel (N = 2L reals -> L + 1 bins, or the inverse).
+const void *mixed_real_kernel(bool inverse);
+
 // LDS elements of the tile data of a workgroup, and total LDS bytes (tile
 // data, the pass-twiddle table that follows it and, for column tiles with the
 // four-step twiddle, kFourStepVals values per line).

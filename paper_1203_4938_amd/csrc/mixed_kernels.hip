@@ -12,6 +12,7 @@
 #include <string>
 
 #include "mixed_device.h"
+#include "real_pair.h"
 
 namespace dpfft {
 
@@ -44,6 +45,85 @@ __global__ void __launch_bounds__(1024) k_mixed(const cf *__restrict__ in, cf *_
   t.valid2 = tid < mp.C * mp.T && line0 + t.c2 < a.lines;
   t.dst2 = out + bb * a.out_b + (line0 + t.c2) * a.out_l;
   mixed_tile<MAP, OMAP, TW4, SW>(sh, t, lds, mp.C * mp.T);
+}
+
+// Real rows: lines of N = 2L reals <-> L + 1 bins, L 7-smooth, the L-point
+// transform of the samples read as complex pairs and the pairing of k with
+// L - k in one launch (tw4_lo, tw4_hi: the two-level table of w_N).  Forward,
+// every pass leaves its outputs in LDS and the pairing reads both elements
+// of a pair there; inverse, the pairs are formed on the way in, swapped for
+// the swap(FFT(swap)) form, and the first pass reads them from LDS.  A
+// separate pairing launch moves the line through HBM once more: 16 images of
+// 1080 x 1920: rows and pairing launches 53 + 41 us, 63 us fused (inverse 39 +
+// 52 us, 70 us).
+template <bool INV>
+__global__ void __launch_bounds__(1024) k_mixed_real(const cf *__restrict__ in,
+                                                     cf *__restrict__ out, MixedArgs a) {
+  extern __shared__ cf lds[];
+  const MixedPlan &mp = a.mp;
+  const int tid = threadIdx.x, L = mp.L, T = mp.T;
+  const int64_t bb = blockIdx.x / a.tiles_per_batch;
+  const int64_t line0 = (int64_t)(blockIdx.x - bb * a.tiles_per_batch) * mp.C;
+  const int c = tid / T, j = tid % T;
+  const bool valid = tid < mp.C * T && line0 + c < a.lines;
+  const cf *src = in + bb * a.in_b + (line0 + c) * a.in_l;
+  cf *dst = out + bb * a.out_b + (line0 + c) * a.out_l;
+  lcf *row = as_lds(lds) + c * mp.pitch;
+  const uint32_t msk = (1u << a.tw4_shift) - 1u;
+  auto wn = [&](int k) { return cmul(a.tw4_hi[(uint32_t)k >> a.tw4_shift], a.tw4_lo[(uint32_t)k & msk]); };
+
+  lcf *twl = as_lds(lds) + mp.tw_lds;
+  const int ntw = tw2_entries(L, mp.tw2_shift), nth = mp.C * T;
+  int ntw0 = 0;  // table entries the first pass copies
+  if constexpr (INV) {
+    for (int i = tid; i < ntw; i += nth) stc(twl, i, a.tw2[i]);
+    if (valid) {
+      for (int k = j; k <= L / 2; k += T) {
+        cf xk = src[k], xr = src[L - k], zk, zr;
+        if (k == 0) xk.y = xr.y = 0.f;
+        real_pair_inv(xk, xr, wn(k), zk, zr);
+        stc(row, k + (k >> 4), cswap(zk));
+        const int r = L - k;
+        if (k != 0 && r != k) stc(row, r + (r >> 4), cswap(zr));
+      }
+    }
+    __syncthreads();
+  } else {
+    ntw0 = ntw < nth ? ntw : nth;
+    for (int i = tid + nth; i < ntw; i += nth) stc(twl, i, a.tw2[i]);
+    if (mp.P == 0) {
+      if (valid && j == 0) stc(row, 0, src[0]);
+      __syncthreads();
+    }
+  }
+  if (INV && mp.P == 0) {
+    if (valid && j == 0) dst[0] = cscale(cswap(ldc(row, 0)), a.scale);
+    return;
+  }
+  int ns = 1;
+  for (int p = 0; p < mp.P; ++p) {
+    const int R = (int)((mp.codes >> (5 * p)) & 31u);
+    mixed_pass_any<ELEM_FAST, ELEM_FAST, TW4_NONE>(
+        R, as_glb(src), as_glb(dst), as_lds(lds), twl, as_glb(a.tw2), ntw0, nullptr, nullptr, twl, L, T,
+        mp.C, mp.pitch, ns, mp.tw2_shift, 0, c, j, valid, !INV && p == 0, INV && p == mp.P - 1,
+        INV ? 2 : 0, 1, 1, 0, a.scale);
+    ns *= R;
+  }
+  if constexpr (!INV) {
+    if (valid) {
+      for (int k = j; k <= L / 2; k += T) {
+        const int r = L - k, rz = k == 0 ? 0 : r;
+        cf xk, xr;
+        real_pair_fwd(ldc(row, k + (k >> 4)), ldc(row, rz + (rz >> 4)), wn(k), xk, xr);
+        dst[k] = xk;
+        if (r != k) dst[r] = xr;
+      }
+    }
+  }
+}
+
+const void *mixed_real_kernel(bool inverse) {
+  return inverse ? (const void *)&k_mixed_real<true> : (const void *)&k_mixed_real<false>;
 }
 
 // ---------------------------------------------------------------------------

@@ -109,6 +109,25 @@ struct MixedStep : Step {
   hipError_t prepare() const override;
 };
 
+// Real rows on the runtime-radix passes: N = 2L reals <-> L + 1 bins, the
+// pairing in LDS (each step list is used for one direction only).
+struct MixedRealStep : Step {
+  MixedArgs a{};
+  bool inv = false;
+  dim3 grid;
+  int threads = 0;
+  int lds_bytes = 0;
+  int src = BUF_IN, dst = BUF_OUT;
+  size_t tw2_off = 0, lo_off = 0, hi_off = 0;
+  std::string name;
+  void bind(const float2 *tables) override;
+  hipError_t launch(const ExecCtx &ctx) const override;
+  std::string describe() const override;
+  void extent(int64_t &max_in, int64_t &max_out, int &src_id, int &dst_id) const override;
+  bool valid() const override;
+  hipError_t prepare() const override;
+};
+
 struct MfmaStep : Step {
   MfmaArgs a{};
   int prec = 0;

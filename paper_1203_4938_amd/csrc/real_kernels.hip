@@ -20,6 +20,7 @@
 // Hermitian spectrum are real; their imaginary parts are ignored.
 #include "line_device.h"
 #include "real.h"
+#include "real_pair.h"
 
 namespace dpfft {
 
@@ -119,12 +120,7 @@ __global__ void __launch_bounds__(C * (P2<L>::T))
 // lengths that are not powers of two: the L-point complex transform of z runs
 // as launches of its own (the four-step pair, or the runtime-radix single
 // pass), and this pass pairs the elements k and L - k that the in-kernel form
-// pairs through LDS.  With Fe[L-k] = conj Fe[k], Fo[L-k] = conj Fo[k] and w_N^{L-k} =
-// -conj w_N^k, one twiddle serves both outputs of a pair:
-//   X[k] = Fe[k] + w_N^k Fo[k],   X[L-k] = conj(Fe[k] - w_N^k Fo[k])
-// (k = 0: X[L], from Z[0] alone; for even L, k = L/2 pairs with itself).  The inverse
-// forms Fe' + i Fo' at k and L - k the same way (its conjugate halves) for the
-// complex inverse, which holds the samples once scaled by 1/N.  A thread
+// pairs through LDS (real_pair.h).  A thread
 // reads both elements of its pair before it writes them, so the pass would
 // also be correct in place; in and out are not restrict-qualified.
 template <bool INV>
@@ -140,21 +136,20 @@ __global__ void __launch_bounds__(256) k_real_pair(const cf *in, cf *out, RealPa
     cf *dst = out + b * a.out_b;
     if constexpr (!INV) {
       const cf zk = src[k], zr = src[kr == a.L ? 0 : kr];
-      const cf fe = make_float2(0.5f * (zk.x + zr.x), 0.5f * (zk.y - zr.y));
-      const cf fo = make_float2(0.5f * (zk.y + zr.y), -0.5f * (zk.x - zr.x));
-      const cf t = cmul(w, fo);
-      dst[k] = cadd(fe, t);
-      if (kr != k) dst[kr] = make_float2(fe.x - t.x, t.y - fe.y);
+      cf xk, xr;
+      real_pair_fwd(zk, zr, w, xk, xr);
+      dst[k] = xk;
+      if (kr != k) dst[kr] = xr;
     } else {
       cf xk = src[k], xr = src[kr];
       if (k == 0) {  // bins 0 and L of a Hermitian spectrum are real
         xk.y = 0.f;
         xr.y = 0.f;
       }
-      const cf fe = make_float2(xk.x + xr.x, xk.y - xr.y);                   // X[k] + conj X[L-k]
-      const cf fo = cmul(make_float2(xk.x - xr.x, xk.y + xr.y), make_float2(w.x, -w.y));
-      dst[k] = make_float2(fe.x - fo.y, fe.y + fo.x);                        // Fe' + i Fo'
-      if (k != 0 && kr != k) dst[kr] = make_float2(fe.x + fo.y, fo.x - fe.y);  // conj Fe' + i conj Fo'
+      cf zk, zr;
+      real_pair_inv(xk, xr, w, zk, zr);
+      dst[k] = zk;
+      if (k != 0 && kr != k) dst[kr] = zr;
     }
   }
 }

@@ -1,6 +1,7 @@
 """GPU parity of the wide runtime-radix passes (radices 6, 10, 12, 14, 15, 18,
 20, 21, 24, 25) alone, in every position and with partly idle threads; of the
-four-step twiddles after each kind of last pass.  Against the FP64 oracle, rel L2 <= 1e-5 per signal."""
+four-step twiddles after each kind of last pass; and of the real rows that
+pair their bins in LDS.  Against the FP64 oracle, rel L2 <= 1e-5 per signal."""
 import numpy as np
 import pytest
 
@@ -49,6 +50,28 @@ def test_four_step(n, batch, order, monkeypatch):
         e = max_rel(run_plan(p, xd, inverse=inv).cpu().numpy(), oracle.fft_batch(x, inverse=inv))
         say(f"   inverse={inv}: {e:.3e}")
         assert e <= TOL_FP32, (n, inv, e)
+
+
+@pytest.mark.parametrize("ny,nx,b", [(3, 2, 5), (5, 4, 3), (7, 6, 3), (9, 50, 4), (6, 1250, 3),
+                                     (5, 1920, 3), (1080, 18, 2), (2160, 30, 1), (3, 32400, 2)])
+def test_real_rows(ny, nx, b):
+    """Half rows of one point, odd lengths (no self-paired middle bin), even
+    ones, several lines per workgroup with a ragged last one, the longest."""
+    import torch
+
+    import paper_1203_4938_amd as dp
+    g = np.random.default_rng(ny * 7919 + nx)
+    x = g.uniform(-1, 1, (b, ny, nx)).astype(np.float32)
+    p = dp.Plan(shape=(ny, nx), batch=b, rank=2, real=True)
+    say("[real rows]", p.describe().replace("\n", " | "))
+    spec = p.exec(torch.from_numpy(x).cuda())
+    back = p.exec(spec, inverse=True)
+    torch.cuda.synchronize()
+    ref = oracle.fft2d(x.astype(np.complex64))[:, :, : nx // 2 + 1]
+    ef = oracle.rel_l2_f32(spec.cpu().numpy(), ref)
+    eb = oracle.rel_l2_f32(back.cpu().numpy().astype(np.complex64), x.astype(np.complex128))
+    say(f"   forward max {ef.max():.3e} round trip max {eb.max():.3e}")
+    assert ef.max() <= TOL_FP32 and eb.max() <= TOL_FP32
 
 
 def test_ragged_every_column_length():

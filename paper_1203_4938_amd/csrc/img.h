@@ -10,7 +10,6 @@ constexpr int kImgTileH = 16;         // pixels per front-end tile, y
 constexpr int kImgThreads = 256;
 constexpr int kImgBlocksPerGroup = 256;  // 4x4 blocks per workgroup of the block-list kernels
 constexpr int kImgAssignBlocks = 1024;   // 4x4 blocks per workgroup of the assignment
-constexpr int kImgLdsSumK = 128;         // up to this k the assignment sums in LDS
 constexpr int kImgMaxK = 256;
 
 struct ImgArgs {
@@ -19,7 +18,7 @@ struct ImgArgs {
   int32_t *code;
   int32_t *wgcount;    // per image: per block group, pattern blocks (then their offsets)
   int32_t *npat;       // per image: pattern blocks
-  float *part;         // per image, per assignment group: k x 17 partial sums and counts
+  float *part;         // per image and codeword, per assignment group: 17 partial sums and count
   int64_t h, w;        // pixels
   int64_t nb;          // blocks per image ((h/4) (w/4))
   int32_t groups;      // block groups per image (ceil(nb / 256))
@@ -35,7 +34,7 @@ const void *img_kernel_front();
 const void *img_kernel_count();
 const void *img_kernel_scan();
 const void *img_kernel_seed();
-const void *img_kernel_assign(bool accumulate);
+const void *img_kernel_assign(bool accumulate, int k);
 const void *img_kernel_update();
 size_t img_assign_lds_bytes(int k, bool accumulate);
 

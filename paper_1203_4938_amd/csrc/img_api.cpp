@@ -91,10 +91,10 @@ std::vector<Launch> sequence(const img_desc_t *d, const ImgArgs &a) {
   v.push_back({img_kernel_scan(), dim3(B), 256, 0});
   v.push_back({img_kernel_seed(), gb, kImgBlocksPerGroup, 0});
   for (int it = 0; it < d->iters; ++it) {
-    v.push_back({img_kernel_assign(true), ga, kImgThreads, img_assign_lds_bytes(a.k, true)});
+    v.push_back({img_kernel_assign(true, a.k), ga, kImgThreads, img_assign_lds_bytes(a.k, true)});
     v.push_back({img_kernel_update(), gu, 256, 0});
   }
-  v.push_back({img_kernel_assign(false), ga, kImgThreads, img_assign_lds_bytes(a.k, false)});
+  v.push_back({img_kernel_assign(false, a.k), ga, kImgThreads, img_assign_lds_bytes(a.k, false)});
   return v;
 }
 
@@ -265,7 +265,7 @@ fft_status_t img_encode(const img_desc_t *desc, const float *dev, const float *a
   a.act = const_cast<float *>(act);
   a.codebook = const_cast<float *>(codebook);
   a.code = code;
-  const hipError_t e = launch(img_kernel_assign(false), dim3((unsigned)a.agroups, (unsigned)desc->batch),
+  const hipError_t e = launch(img_kernel_assign(false, a.k), dim3((unsigned)a.agroups, (unsigned)desc->batch),
                               kImgThreads, a, (hipStream_t)hip_stream, img_assign_lds_bytes(a.k, false));
   if (e != hipSuccess) return fail(FFT_E_DEVICE, std::string("launch: ") + hipGetErrorString(e));
   return FFT_OK;

@@ -481,6 +481,23 @@ bool choose_line(int L, int map, int omap, bool tw4, int cmax, int step, int64_t
       *out = k;
     }
   }
+  // A column or transposed-row launch of fewer tiles than CUs takes the widest
+  // narrower tile that gives every CU one, or the narrowest there is.  Measured
+  // (whole transform, tiles of 16, 8, 4): 2^18 points alone 14.2, 11.9, 11.6 us,
+  // 4 of them 16.1, 14.1, 16.7; 2^20 alone 24.2, 19.9, 19.7, 2 of them 28.9,
+  // 26.9, 28.5, 4 of them (256 tiles of 16) 32.1, 32.4, 35.5.
+  const bool tiles_free = ov.c[step] < 0 && ov.p[step] < 0 && ov.t[step] < 0 && ov.h[step] < 0;
+  auto tiles = [&](int C) { return (lines_total + C - 1) / C; };
+  if (best >= 0 && tiles_free && (map == LINE_FAST || omap == LINE_FAST) &&
+      tiles(out->lines) < t_cus) {
+    const int wide = out->lines;
+    for (int i = 0; i < n; ++i) {
+      const KernelInfo &k = cand[i];
+      if (k.persistent || k.ept != 16 || k.sub != 1 || k.lines >= wide) continue;
+      const bool fills = tiles(k.lines) >= t_cus, filled = tiles(out->lines) >= t_cus;
+      if (fills ? (!filled || k.lines > out->lines) : (!filled && k.lines < out->lines)) *out = k;
+    }
+  }
   return best >= 0;
 }
 

@@ -525,6 +525,16 @@ static const LineEntry kLineTable[] = {
     ROWT(64, 16), ROWT(128, 16), ROWT(256, 32), ROWT(512, 16),
     ROWT(1024, 16), ROWT(1024, 8), ROWT(2048, 4), ROWT(2048, 8), ROWT(4096, 4),
 };
+// Narrow tiles for batches whose tiles would leave CUs idle (the planner takes
+// them only there): what one workgroup moves then sets the launch's time (2^20
+// points alone, 1024 x 1024: tiles of 16 10.1 + 10.8 us, tiles of 4 below 8 each).
+static const LineEntry kLineTableNarrow[] = {
+    COL(128, 8), COL(128, 4), COL(256, 8), COL(256, 4), COL(512, 8), COL(512, 4), COL(1024, 4),
+    COLTW(128, 8), COLTW(128, 4), COLTW(256, 8), COLTW(256, 4), COLTW(512, 8), COLTW(512, 4),
+    COLTW(1024, 4), COLTW(2048, 2),
+    ROWT(128, 8), ROWT(128, 4), ROWT(256, 8), ROWT(256, 4), ROWT(512, 8), ROWT(512, 4),
+    ROWT(1024, 4), ROWT(2048, 2),
+};
 // nontemporal tile data (rows of 2048, the 256 x 256 four-step): 2-4% faster
 #undef KNT
 #define KNT 3
@@ -673,6 +683,7 @@ static void fill(const LineEntry &e, KernelInfo *out) {
 template <class F>
 static void for_each_entry(F f) {
   for (const auto &e : kLineTable) f(e);
+  for (const auto &e : kLineTableNarrow) f(e);
   for (const auto &e : kLineTableNt) f(e);
   for (const auto &e : kLineTable32Pref) f(e);
   for (const auto &e : kLineTable32) f(e);

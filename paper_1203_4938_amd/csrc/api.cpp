@@ -1050,11 +1050,11 @@ fft_status_t plan_mfma_1d(dpfft_plan_s *P) {
   return FFT_OK;
 }
 
-// Real-input row step: lines of N = 2L reals <-> L + 1 bins.  `rows` lines per
-// batch item, items `real_b` float pairs apart on the real side and `cplx_b`
-// complex elements apart on the spectrum side.
+// Real-input row step: lines of N = 2L reals <-> L + 1 bins.  `rows` lines in
+// each of `items` batch items, items `real_b` float pairs apart on the real
+// side and `cplx_b` complex elements apart on the spectrum side.
 std::unique_ptr<RealStep> make_real(dpfft_plan_s *P, const char *name, int64_t N, bool inv,
-                                    int64_t rows, int64_t real_b, int64_t cplx_b) {
+                                    int64_t items, int64_t rows, int64_t real_b, int64_t cplx_b) {
   auto s = std::make_unique<RealStep>();
   const int L = (int)(N / 2);
   if (!real_kernel(L, &s->k)) return nullptr;
@@ -1086,7 +1086,7 @@ std::unique_ptr<RealStep> make_real(dpfft_plan_s *P, const char *name, int64_t N
   s->a.in_e = s->a.out_e = 1;
   s->a.lines = rows;
   s->a.tiles_per_batch = (rows + C - 1) / C;
-  s->grid = dim3((unsigned)(P->batch * s->a.tiles_per_batch));
+  s->grid = dim3((unsigned)(items * s->a.tiles_per_batch));
   s->a.ntiles = s->grid.x;
   s->a.scale = inv ? (float)(1.0 / (double)N) : 1.0f;
   return s;
@@ -1202,8 +1202,8 @@ fft_status_t plan_real_1d(dpfft_plan_s *P) {
     P->variant = "real " + core + " + pairing";
     return FFT_OK;
   }
-  auto f = make_real(P, "real_forward", N, false, B, 0, 0);
-  auto i = make_real(P, "real_inverse", N, true, B, 0, 0);
+  auto f = make_real(P, "real_forward", N, false, 1, B, 0, 0);
+  auto i = make_real(P, "real_inverse", N, true, 1, B, 0, 0);
   if (!f || !i) return fail(FFT_E_UNSUPPORTED, "no real-input kernel for N=" + std::to_string(N));
   P->steps.push_back(std::move(f));
   P->isteps.push_back(std::move(i));
@@ -1301,8 +1301,8 @@ fft_status_t plan_real_2d(dpfft_plan_s *P) {
   if (!is_pow2(NY) || !is_pow2(NX)) return plan_real_2d_mixed(P);
   const int64_t W = NX / 2 + 1;  // bins per row
   const Override ov = read_override();
-  auto rf = make_real(P, "real_rows", NX, false, NY, NY * NX / 2, NY * W);
-  auto ri = make_real(P, "real_rows_inverse", NX, true, NY, NY * NX / 2, NY * W);
+  auto rf = make_real(P, "real_rows", NX, false, B, NY, NY * NX / 2, NY * W);
+  auto ri = make_real(P, "real_rows_inverse", NX, true, B, NY, NY * NX / 2, NY * W);
   if (!rf || !ri) return fail(FFT_E_UNSUPPORTED, "no real-input row kernel for nx=" + std::to_string(NX));
   std::unique_ptr<LineStep> cf, ci;
   if (NY > 1) {

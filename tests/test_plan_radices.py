@@ -70,3 +70,12 @@ def test_ragged_workspace():
         for b in (1, (8 << 20) // pad, (8 << 20) // n, (8 << 20) // n + 1):
             want = n if b * n <= 8 << 20 < b * pad else pad
             assert f"workspace={8 * b * want}B" in _dry(ragged_sizes=[n] * b), (n, b)
+
+
+def test_real_signals_cover_the_batch_once():
+    """Real signals of a power of two: one workgroup per C signals."""
+    import paper_1203_4938_amd as dp
+    for n, batch in ((2, 1000), (128, 19912), (2048, 1447), (32768, 7)):
+        text = _dry(n=n, batch=batch, flags=dp.FFT_F_REAL)
+        for m in re.finditer(r"real_(?:forward|inverse): .*? C=(\d+) threads=\d+ grid=(\d+)", text):
+            assert int(m.group(2)) == -(-batch // int(m.group(1))), text

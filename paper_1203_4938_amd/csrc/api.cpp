@@ -1092,6 +1092,42 @@ std::unique_ptr<RealStep> make_real(dpfft_plan_s *P, const char *name, int64_t N
   return s;
 }
 
+// Real rows of nx = 2L samples <-> L + 1 bins with the pairing in LDS,
+// `rows` per batch item; the real side is dense, the spectrum side has its
+// rows `pitch` elements apart.
+std::unique_ptr<MixedRealStep> make_mixed_real(dpfft_plan_s *P, const char *name, int64_t L,
+                                               bool inv, int64_t rows, int64_t pitch, int C,
+                                               size_t lo_off, size_t hi_off, int shift) {
+  auto m = make_mixed(P, name, L, ELEM_FAST, ELEM_FAST, false, C);
+  if (!m) return nullptr;
+  auto s = std::make_unique<MixedRealStep>();
+  s->a = m->a;
+  s->inv = inv;
+  s->threads = m->threads;
+  s->lds_bytes = m->lds_bytes;
+  s->tw2_off = m->tw2_off;
+  s->lo_off = lo_off;
+  s->hi_off = hi_off;
+  s->name = name;
+  s->a.tw4_shift = shift;
+  s->a.in_b = s->a.out_b = 0;
+  s->a.in_l = inv ? pitch : L;
+  s->a.out_l = inv ? L : pitch;
+  s->a.in_e = s->a.out_e = 1;
+  s->a.lines = rows;
+  s->a.tiles_per_batch = (rows + C - 1) / C;
+  s->grid = dim3((unsigned)s->a.tiles_per_batch);
+  s->a.scale = inv ? (float)(1.0 / (double)(2 * L)) : 1.0f;
+  return s;
+}
+
+// Signals from which the 7-smooth single-pass core pairs its bins in LDS, one
+// launch and no workspace: 100,000 signals of 70 samples 53 us in two launches,
+// 21 in one, 2000 of 30000 266 us, 200.  Smaller batches keep the
+// core and the pairing launch their plans are described with (3 signals of
+// 1000: 8.9 us either way).
+constexpr int64_t kPairInLds = 4;
+
 // Real-input batch of 1D signals: one launch per direction while the
 // N/2-point complex core fits one workgroup; above, the core is the
 // four-step pair of launches and the pairing of k with N/2 - k a launch of its
@@ -1127,6 +1163,18 @@ fft_status_t plan_real_1d(dpfft_plan_s *P) {
       return r;
     };
     std::string core;
+    if (L <= kSinglePassMax && !is_pow2(L) && B >= kPairInLds) {
+      const int C = mixed_c(ov, 0, mixed_row_lines(L), L, ELEM_FAST, ELEM_FAST);
+      for (int i = 0; i < 2; ++i) {
+        auto r = C ? make_mixed_real(P, i ? "real_rows_inverse" : "real_rows", L, i == 1, B, L + 1, C,
+                                     lo_off, hi_off, shift)
+                   : nullptr;
+        if (!r) return fail(FFT_E_UNSUPPORTED, "no runtime-radix rows for real N=" + std::to_string(N));
+        (i ? P->isteps : P->steps).push_back(std::move(r));
+      }
+      P->variant = "real runtime-radix single-pass";
+      return FFT_OK;
+    }
     if (L <= kSinglePassMax && !is_pow2(L)) {
       // single-pass runtime-radix core: input -> workspace (forward), and
       // workspace -> output after the pairing (inverse), never in place
@@ -1209,35 +1257,6 @@ fft_status_t plan_real_1d(dpfft_plan_s *P) {
   P->isteps.push_back(std::move(i));
   P->variant = "real single-pass";
   return FFT_OK;
-}
-
-// Real rows of nx = 2L samples <-> L + 1 bins with the pairing in LDS,
-// `rows` per batch item; the real side is dense, the spectrum side has its
-// rows `pitch` elements apart.
-std::unique_ptr<MixedRealStep> make_mixed_real(dpfft_plan_s *P, const char *name, int64_t L,
-                                               bool inv, int64_t rows, int64_t pitch, int C,
-                                               size_t lo_off, size_t hi_off, int shift) {
-  auto m = make_mixed(P, name, L, ELEM_FAST, ELEM_FAST, false, C);
-  if (!m) return nullptr;
-  auto s = std::make_unique<MixedRealStep>();
-  s->a = m->a;
-  s->inv = inv;
-  s->threads = m->threads;
-  s->lds_bytes = m->lds_bytes;
-  s->tw2_off = m->tw2_off;
-  s->lo_off = lo_off;
-  s->hi_off = hi_off;
-  s->name = name;
-  s->a.tw4_shift = shift;
-  s->a.in_b = s->a.out_b = 0;
-  s->a.in_l = inv ? pitch : L;
-  s->a.out_l = inv ? L : pitch;
-  s->a.in_e = s->a.out_e = 1;
-  s->a.lines = rows;
-  s->a.tiles_per_batch = (rows + C - 1) / C;
-  s->grid = dim3((unsigned)s->a.tiles_per_batch);
-  s->a.scale = inv ? (float)(1.0 / (double)(2 * L)) : 1.0f;
-  return s;
 }
 
 // Real-input images whose sides are not both powers of two, on the

@@ -74,6 +74,26 @@ def test_real_rows(ny, nx, b):
     assert ef.max() <= TOL_FP32 and eb.max() <= TOL_FP32
 
 
+@pytest.mark.parametrize("n", [6, 14, 18, 70, 250, 1000, 9450, 30000, 32400])
+def test_real_signals(n):
+    """7-smooth real signals, batches from which the bins are paired in LDS."""
+    import torch
+
+    import paper_1203_4938_amd as dp
+    for batch in (4, 37):
+        x = np.random.default_rng(n).uniform(-1, 1, (batch, n)).astype(np.float32)
+        p = dp.Plan(n, batch, real=True)
+        say("[real signals]", p.describe().replace("\n", " | "))
+        assert p.num_steps() == 1 and p.workspace_bytes == 0
+        spec = p.exec(torch.from_numpy(x).cuda())
+        back = p.exec(spec, inverse=True)
+        torch.cuda.synchronize()
+        ref = oracle.fft_batch(x.astype(np.complex64))[:, : n // 2 + 1]
+        ef = oracle.rel_l2_f32(spec.cpu().numpy(), ref)
+        eb = oracle.rel_l2_f32(back.cpu().numpy().astype(np.complex64), x.astype(np.complex128))
+        assert ef.max() <= TOL_FP32 and eb.max() <= TOL_FP32, (n, batch, ef.max(), eb.max())
+
+
 def test_ragged_every_column_length():
     """Four-step signals whose column and row lines take every compile-time
     length, their intermediate rows padded to whole lines."""

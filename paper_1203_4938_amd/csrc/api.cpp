@@ -387,6 +387,47 @@ std::string RealPairStep::describe() const {
   return o.str();
 }
 
+void RealFourStep::bind(const float2 *tables) {
+  a.tw = tables + tw_off;
+  a.tw2 = tables + tw2_off;
+  a.wlo = tables + wlo_off;
+  a.whi = tables + whi_off;
+  a.tw4_lo = tables + tw4_lo_off;
+  a.tw4_hi = tables + tw4_hi_off;
+}
+
+hipError_t RealFourStep::launch(const ExecCtx &ctx) const {
+  const float2 *s = buf_c(ctx, src, 0);
+  float2 *d = buf_m(ctx, dst, 0);
+  RealFourArgs args = a;
+  void *kargs[] = {(void *)&s, (void *)&d, (void *)&args};
+  const dim3 grid(std::min<uint32_t>(a.ntiles, (uint32_t)resident));
+  return hipLaunchKernel(inv ? k.cols : k.rows, grid, dim3(k.threads), kargs, 0, ctx.stream);
+}
+
+void RealFourStep::extent(int64_t &max_in, int64_t &max_out, int &src_id, int &dst_id) const {
+  // the spectrum side holds bins 0..L, the intermediate L values
+  max_in = (batch - 1) * a.in_b + (inv ? (int64_t)a.L : (int64_t)a.L - 1);
+  max_out = (batch - 1) * a.out_b + (inv ? (int64_t)a.L - 1 : (int64_t)a.L);
+  src_id = src;
+  dst_id = dst;
+}
+
+bool RealFourStep::valid() const {
+  // whole tiles, 32-bit offsets within a signal and tile numbers
+  return k.rows && k.cols && k.L > 0 && (int64_t)k.L * a.n == a.L && a.n % k.lines == 0 &&
+         a.L < (1u << 29) && batch * (a.n / k.lines) == (int64_t)a.ntiles &&
+         (int64_t)a.ntiles + resident < (int64_t(1) << 32) && resident > 0;
+}
+
+std::string RealFourStep::describe() const {
+  std::ostringstream o;
+  o << name << ": L=" << k.L << " (N=" << 2 * (int64_t)a.L << ") pairs in LDS C=" << k.lines
+    << " threads=" << k.threads << " persistent tiles=" << a.ntiles << " grid<=" << resident
+    << " lds=" << (inv ? k.lds_cols : k.lds_rows) << "B";
+  return o.str();
+}
+
 }  // namespace dpfft
 
 dpfft_plan_s::~dpfft_plan_s() {
@@ -1121,6 +1162,80 @@ std::unique_ptr<MixedRealStep> make_mixed_real(dpfft_plan_s *P, const char *name
   return s;
 }
 
+// Core points of a batch from which the passes of a power-of-two four-step core
+// pair the bins in their tiles, for cores of 2^17 to 2^21 points.  Measured,
+// forward + inverse, three launches against two: 32 x 2^22 samples 690 + 689 us,
+// 655 + 575; 32 x 2^21 341 + 337, 328 + 274; 64 x 2^20 322 + 321, 294 + 260;
+// 128 x 2^19 295 + 294, 263 + 253; 256 x 2^18 275 + 275, 261 + 219; shorter cores
+// leave the other pass lines of 128 points and gain nothing (512 x 2^17 269 +
+// 263, 270 + 253).  Near the line 2 x 2^21 took 38 + 36 and takes 31 + 33, 17 x 2^18
+// 38 + 30 and 28 + 25; smaller batches are bound by their launches' fixed
+// times and keep the three that their plans are described with.
+constexpr int64_t kPairInTiles = int64_t(1) << 21;
+
+// Long real signals of power-of-two length in two launches per direction.
+// Forward: columns input -> workspace, rows with the pairing workspace ->
+// output; inverse: columns with the pairing input -> workspace, rows workspace
+// -> output (scale 1/N).  A geometry that the caller or the tuner chose is for
+// the core's own two passes, so it keeps them.  The paired pass takes lines of
+// 512 points (its tiles hold 32 of them) while the other side's stay within
+// 1024, else of 1024; `done` stays false where the other side's lines have no
+// instance.
+fft_status_t plan_real_fourstep(dpfft_plan_s *P, bool *done) {
+  const int64_t N = P->n, B = P->batch, L = N / 2;
+  const Override ov = read_override();
+  const int lg = ilog2(L), lgp = lg < 20 ? 9 : 10, lgo = lg - lgp;
+  RealFourKernel k;
+  if (!ov.empty() || lgo < 8 || lgo > 11 || !real_four_kernel(1 << lgp, &k)) return FFT_OK;
+  for (int i = 0; i < 2; ++i) {
+    Override o = ov;
+    o.split = i ? lgp : lgo;  // forward: the rows pair, inverse: the columns
+    std::unique_ptr<LineStep> a, b;
+    if (!fourstep_steps(P, L, B, i ? L + 1 : L, i ? L : L + 1, o, a, b))
+      return fail(FFT_E_UNSUPPORTED, "no four-step kernels for the real-input core L=" + std::to_string(L));
+    auto r = std::make_unique<RealFourStep>();
+    r->k = k;
+    r->inv = i == 1;
+    r->batch = B;
+    r->resident = resident_for(i ? k.lds_cols : k.lds_rows, k.threads);
+    r->a.n = 1u << lgo;
+    r->a.L = (uint32_t)L;
+    r->a.ntiles = (uint32_t)(B * (r->a.n / k.lines));
+    r->a.in_b = i ? L + 1 : L;
+    r->a.out_b = i ? L : L + 1;
+    r->tw_off = P->tables.add(stockham_table_pow2(k.L, k.ept));
+    std::vector<std::complex<double>> lo, hi;
+    fourstep_tables(k.L, tw2_shift(lgp), lo, hi);
+    lo.insert(lo.end(), hi.begin(), hi.end());
+    r->tw2_off = P->tables.add(lo);
+    fourstep_tables(N, lgo, lo, hi);
+    r->wlo_off = P->tables.add(lo);
+    r->whi_off = P->tables.add(hi);
+    r->a.tw4_shift = a->a.tw4_shift;
+    r->tw4_lo_off = a->tw4_lo_off;
+    r->tw4_hi_off = a->tw4_hi_off;
+    r->src = i ? BUF_IN : BUF_WS;
+    r->dst = i ? BUF_WS : BUF_OUT;
+    if (i == 0) {
+      a->name = "real_core_columns";
+      r->name = "real_rows_paired";
+      P->steps.push_back(std::move(a));
+      P->steps.push_back(std::move(r));
+    } else {
+      r->name = "real_columns_paired_inverse";
+      b->name = "real_core_rows_transposed_inverse";
+      b->inv_scale = (float)(1.0 / (double)N);
+      P->isteps.push_back(std::move(r));
+      P->isteps.push_back(std::move(b));
+    }
+  }
+  P->ws_bytes = (size_t)B * (size_t)L * sizeof(float2);
+  P->variant = "real four-step " + std::to_string(1 << lgo) + "x" + std::to_string(1 << lgp) +
+               ", pairing in the tiles";
+  *done = true;
+  return FFT_OK;
+}
+
 // Signals from which the 7-smooth single-pass core pairs its bins in LDS, one
 // launch and no workspace: 100,000 signals of 70 samples 53 us in two launches,
 // 21 in one, 2000 of 30000 266 us, 200.  Smaller batches keep the
@@ -1140,6 +1255,11 @@ constexpr int64_t kPairInLds = 4;
 // into it, scaled by 1/N.
 fft_status_t plan_real_1d(dpfft_plan_s *P) {
   const int64_t N = P->n, B = P->batch;
+  if (is_pow2(N) && N / 2 > kSinglePassMax && B * (N / 2) >= kPairInTiles) {
+    bool done = false;
+    const fft_status_t st = plan_real_fourstep(P, &done);
+    if (st != FFT_OK || done) return st;
+  }
   if (!is_pow2(N) || N / 2 > kSinglePassMax) {
     const int64_t L = N / 2;
     const Override ov = read_override();

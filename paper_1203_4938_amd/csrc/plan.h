@@ -182,6 +182,24 @@ struct RealPairStep : Step {
   bool valid() const override;
 };
 
+// A four-step pass of a real transform's core with the pairing of bins in it:
+// the forward's rows or (inv) the inverse's columns.
+struct RealFourStep : Step {
+  RealFourKernel k{};
+  RealFourArgs a{};
+  bool inv = false;
+  int64_t batch = 0;
+  int resident = 0;
+  int src = BUF_IN, dst = BUF_OUT;
+  size_t tw_off = 0, tw2_off = 0, wlo_off = 0, whi_off = 0, tw4_lo_off = 0, tw4_hi_off = 0;
+  std::string name;
+  void bind(const float2 *tables) override;
+  hipError_t launch(const ExecCtx &ctx) const override;
+  std::string describe() const override;
+  void extent(int64_t &max_in, int64_t &max_out, int &src_id, int &dst_id) const override;
+  bool valid() const override;
+};
+
 // Fused convolution launch: a single-pass line (forward, product with the
 // filter spectrum, inverse) or the row launch of the four-step form.
 struct ConvStep : Step {

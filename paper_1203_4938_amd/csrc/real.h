@@ -2,6 +2,7 @@
 // of the compiled instances.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <stdint.h>
 
 namespace dpfft {
 
@@ -33,5 +34,27 @@ struct RealPairArgs {
   int32_t pad;
 };
 const void *real_pair_kernel(bool inverse);
+
+// Four-step passes with the pairing inside (real_fourstep.hip): the forward's
+// rows (n = N1 rows of this length, stored transposed as bins) and the
+// inverse's columns (n = N2 columns of this length, bins to intermediate).
+struct RealFourArgs {
+  int64_t in_b, out_b;           // complex elements between the signals of in and out
+  uint32_t n;                    // lines per signal
+  uint32_t L;                    // points of the core
+  uint32_t ntiles;
+  int32_t tw4_shift;
+  const float2 *tw, *tw2;        // Stockham and two-level pass tables of the line
+  const float2 *wlo, *whi;       // w_N^l for l < n, w_N^{n h}
+  const float2 *tw4_lo, *tw4_hi; // four-step twiddles of L (columns)
+};
+struct RealFourKernel {
+  int L, lines, ept;
+  const void *rows, *cols;
+  int threads, lds_rows, lds_cols;
+};
+// Instance for lines of L points; persistent: launch at most one grid of
+// resident workgroups.
+bool real_four_kernel(int L, RealFourKernel *out);
 
 }  // namespace dpfft

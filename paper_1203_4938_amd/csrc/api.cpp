@@ -1165,13 +1165,21 @@ std::unique_ptr<MixedRealStep> make_mixed_real(dpfft_plan_s *P, const char *name
 // Core points of a batch from which the passes of a power-of-two four-step core
 // pair the bins in their tiles, for cores of 2^17 to 2^21 points.  Measured,
 // forward + inverse, three launches against two: 32 x 2^22 samples 690 + 689 us,
-// 655 + 575; 32 x 2^21 341 + 337, 328 + 274; 64 x 2^20 322 + 321, 294 + 260;
-// 128 x 2^19 295 + 294, 263 + 253; 256 x 2^18 275 + 275, 261 + 219; shorter cores
+// 655 + 575; 32 x 2^21 341 + 337, 305 + 274; 64 x 2^20 322 + 321, 264 + 260;
+// 128 x 2^19 295 + 294, 239 + 253; 256 x 2^18 275 + 275, 207 + 219; shorter cores
 // leave the other pass lines of 128 points and gain nothing (512 x 2^17 269 +
 // 263, 270 + 253).  Near the line 2 x 2^21 took 38 + 36 and takes 31 + 33, 17 x 2^18
 // 38 + 30 and 28 + 25; smaller batches are bound by their launches' fixed
 // times and keep the three that their plans are described with.
 constexpr int64_t kPairInTiles = int64_t(1) << 21;
+
+// Core bytes of a batch for which its rows read the intermediate with
+// non-temporal loads: about the 256 MiB of the last-level cache, where the
+// lines that stay behind are the bins that neighbouring tiles still complete.
+// Forward, 2^20 samples, ordinary loads against non-temporal: 80 MiB 81 us, 85; 128
+// MiB 134, 126; 192 MiB 222, 193; 256 MiB 294, 264; 384 MiB 430, 415; 512 MiB 564, 556
+// (2^21 samples there 645, 653).  256 MiB of 2^18 samples 260, 207; of 2^22 332, 311.
+constexpr int64_t kPairStreamMin = int64_t(128) << 20, kPairStreamMax = int64_t(384) << 20;
 
 // Long real signals of power-of-two length in two launches per direction.
 // Forward: columns input -> workspace, rows with the pairing workspace ->
@@ -1195,6 +1203,7 @@ fft_status_t plan_real_fourstep(dpfft_plan_s *P, bool *done) {
       return fail(FFT_E_UNSUPPORTED, "no four-step kernels for the real-input core L=" + std::to_string(L));
     auto r = std::make_unique<RealFourStep>();
     r->k = k;
+    if (8 * L * B >= kPairStreamMin && 8 * L * B <= kPairStreamMax) r->k.rows = k.rows_nt;
     r->inv = i == 1;
     r->batch = B;
     r->resident = resident_for(i ? k.lds_cols : k.lds_rows, k.threads);

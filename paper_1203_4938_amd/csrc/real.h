@@ -50,7 +50,7 @@ struct RealFourArgs {
 };
 struct RealFourKernel {
   int L, lines, ept;
-  const void *rows, *cols;
+  const void *rows, *rows_nt, *cols;  // rows_nt: the core read with non-temporal loads
   int threads, lds_rows, lds_cols;
 };
 // Instance for lines of L points; persistent: launch at most one grid of

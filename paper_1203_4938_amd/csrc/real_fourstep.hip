@@ -22,6 +22,8 @@
 // kernel: 512-point lines take tiles of 32 (128-byte pieces; with 16, forward
 // 195 us and inverse 142), lines of 1024 fit only 16 (64 bytes: 32 signals of
 // 2^22 samples, 399 us forward where the unpaired rows and the pairing took 452).
+// The rows' loads are non-temporal (rows_nt) where the core is about as large as
+// the 256 MiB last-level cache, so that its lines stay for the bins.
 // One workgroup fits a CU, so the kernels are persistent and prefetch the next
 // tile like the other 1024-point tiles.
 #include "line_device.h"
@@ -68,7 +70,7 @@ __device__ __forceinline__ uint32_t paired_slot() {
   return g % 8u == 0u ? (b % 8u) * (g / 8u) + b / 8u : b;
 }
 
-template <int L, int C, int EPT>
+template <int L, int C, int EPT, int NT>
 __global__ void __launch_bounds__(C * (P2<L, EPT>::T))
     k_real_rows(const cf *__restrict__ in, cf *__restrict__ out, RealFourArgs a) {
   using G = P2<L, EPT>;
@@ -94,7 +96,7 @@ __global__ void __launch_bounds__(C * (P2<L, EPT>::T))
     const uint32_t bb = tl / tpb, t = tl - bb * tpb;
     const cf *src = in + (int64_t)bb * a.in_b + (int64_t)paired_line<C>(t, c, n) * L + j;
 #pragma unroll
-    for (int m = 0; m < E; ++m) x[m] = src[T * m];
+    for (int m = 0; m < E; ++m) x[m] = ld_data<NT>(src + T * m);
   };
   load(tile, v);
 #pragma unroll
@@ -222,7 +224,8 @@ __global__ void __launch_bounds__(C * (P2<L, EPT>::T))
 }
 
 #define RF(L_, C_, E_)                                                                             \
-  RealFourKernel{L_, C_, E_, (const void *)&k_real_rows<L_, C_, E_>,                             \
+  RealFourKernel{L_, C_, E_,                                                                     \
+                 (const void *)&k_real_rows<L_, C_, E_, 0>, (const void *)&k_real_rows<L_, C_, E_, 1>, \
                  (const void *)&k_real_cols<L_, C_, E_>, C_ * P2<L_, E_>::T,                     \
                  8 * (lds_pairs<L_, C_, ELEM_FAST, LINE_FAST>() + L_ +                           \
                       pf_tw_entries<L_, C_, ELEM_FAST, LINE_FAST, E_>()),                        \

@@ -1,6 +1,7 @@
 """Long real signals whose four-step passes pair the bins in their tiles: every
 split the planner makes (512 and 1024-point paired lines, equal and unequal
-sides), batches whose tiles fill the persistent grid unevenly, both directions
+sides), batches whose tiles fill the persistent grid unevenly, both ways of reading
+the intermediate (from 128 MiB on: 129 x 2^18, 65 x 2^20), both directions
 against the oracle, and the imaginary parts of bins 0 and N/2 ignored."""
 import numpy as np
 import pytest
@@ -11,7 +12,8 @@ from gpu_util import TOL_FP32, say
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("lg,batch", [(18, 17), (19, 8), (19, 11), (20, 5), (21, 3), (22, 1), (22, 2)])
+@pytest.mark.parametrize("lg,batch", [(18, 17), (19, 8), (19, 11), (20, 5), (21, 3), (22, 1), (22, 2),
+                                      (18, 129), (20, 65)])
 def test_paired_passes(lg, batch):
     import torch
 

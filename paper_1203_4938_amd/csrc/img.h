@@ -25,6 +25,7 @@ struct ImgArgs {
   int32_t agroups;     // assignment groups per image (ceil(nb / 1024))
   int32_t k;
   float tau;
+  int32_t back;        // assignment: take images and groups from the last to the first
 };
 
 // Kernel entry points, each launched with a grid of (tiles, groups,

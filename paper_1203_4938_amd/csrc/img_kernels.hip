@@ -397,10 +397,11 @@ __global__ void __launch_bounds__(kImgThreads, NI > 8 ? 3 : 4)
   int *wcnt = (int *)(img_lds + ly.wcnt), *woff = (int *)(img_lds + ly.woff);
   int *off = (int *)(img_lds + ly.off);
   uint16_t *idx = (uint16_t *)(img_lds + ly.idx);
-  const int64_t img = blockIdx.y;
+  const uint32_t grp = a.back ? gridDim.x - 1 - blockIdx.x : blockIdx.x;
+  const int64_t img = a.back ? gridDim.y - 1 - blockIdx.y : blockIdx.y;
   const int tid = threadIdx.x;
   const float *gcb = a.codebook + img * (int64_t)k * 16;
-  const int64_t base = (int64_t)blockIdx.x * kImgAssignBlocks;
+  const int64_t base = (int64_t)grp * kImgAssignBlocks;
 
   // a round's vectors: block 32 nt + col of the wave's 64, components 8 hl ..
   // 8 hl + 7 (col = lane & 31, hl = lane >> 5); and the activity of the lane's
@@ -653,7 +654,7 @@ __global__ void __launch_bounds__(kImgThreads, NI > 8 ? 3 : 4)
     for (int i = 0; i < NI; ++i) {
       const int c = g + 16 * i;
       if (c < k) {
-        float *part = a.part + ((img * k + c) * a.agroups + blockIdx.x) * 17;
+        float *part = a.part + ((img * k + c) * a.agroups + grp) * 17;
         part[t] = gs[i];
         if (t == 0) part[16] = (float)gn[i];
       }

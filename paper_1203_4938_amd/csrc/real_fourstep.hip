@@ -15,8 +15,8 @@
 // inverse transform holds the samples, and goes on as the column pass does.
 //
 // Either way the separate launch that moved the whole core through HBM once
-// more is gone: 64 signals of 2^20 samples, forward 104 + 114 + 105 us in three
-// launches, 125 + 169 in two; inverse 103 + 105 + 114, 144 + 114.  HBM bounds the
+// more is gone: 64 signals of 2^20 samples, forward 322 us in three
+// launches, 264 in two (294 with ordinary loads of the rows); inverse 321, 260.  HBM bounds the
 // kernels.  Row pieces are C/2 elements wide, and the bins' rows start at any
 // 8-byte offset, so the forward pieces straddle lines and the store bounds that
 // kernel: 512-point lines take tiles of 32 (128-byte pieces; with 16, forward

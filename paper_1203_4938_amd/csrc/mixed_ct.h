@@ -66,9 +66,14 @@ __device__ __forceinline__ void ct_pass(const CtArgs &a, lcf *lds, lcf *twl, cf 
     if (!act[q]) continue;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      if constexpr (FIRST)
-        v[q][r] = ldc(a.src, (uint32_t)(b + r * M) * a.in_e);
-      else
+      if constexpr (FIRST) {
+        // The inverse's swap belongs here: behind the branch that separates the
+        // loads from the butterflies it costs copies and spills (125 points 124
+        // bytes per lane, 192 points 98 registers for 69; the inverse column
+        // launch of 10,000 signals moved 180 MiB of them each way: 0.366 ms, 0.332 now).
+        const cf x = ldc(a.src, (uint32_t)(b + r * M) * a.in_e);
+        v[q][r] = SW & 1 ? cswap(x) : x;
+      } else
         v[q][r] = ldc(lds, ct_idx<L, MAP>(a.C, a.c, b + r * M));
     }
   }
@@ -78,10 +83,6 @@ __device__ __forceinline__ void ct_pass(const CtArgs &a, lcf *lds, lcf *twl, cf 
 #pragma unroll
   for (int q = 0; q < QM; ++q) {
     if (!act[q]) continue;
-    if constexpr ((SW & 1) && FIRST) {
-#pragma unroll
-      for (int r = 0; r < R; ++r) v[q][r] = cswap(v[q][r]);
-    }
     if constexpr (NS > 1) {
       const int k = (a.j + T * q) % NS;
 #pragma unroll

@@ -116,22 +116,25 @@ typedef struct {
  *                  Hermitian 2D spectrum).
  * Signals (images) are packed back to back on both sides: dist must be 0.
  * Supported: FFT_FP32, rank 1 with N an even number in [2, 2^24] whose
- * prime factors are at most 7 (powers of two up to 32768: one launch per
- * direction; otherwise the N/2-point complex transform of the samples read
- * as N/2 complex pairs runs on launches of its own, one single pass or a
- * four-step pair, and one more launch pairs bin k with N/2 - k, with a
- * workspace of batch * N/2 complex64), rank 2 with nx an even number in
- * [2, 32768] and ny in [1, 16384], both with prime factors <= 7 (powers of
- * two: two launches per direction, the inverse with a workspace of batch *
- * ny * (nx/2 + 1) complex64; other sides: three, the rows of nx/2 pairs on
- * the runtime-radix kernels, the pairing, the columns, with that workspace
- * in both directions).  in != out.  Both buffers are device pointers owned
+ * prime factors are at most 7.  Powers of two up to 32768, and batches of at
+ * least 4 signals of other lengths up to 32768, take one launch per direction.
+ * Longer powers of two from 2^18 to 2^22, in batches of at least 2^22 samples,
+ * take the N/2-point four-step pair with the pairing of bin k with N/2 - k
+ * inside it.  Otherwise the N/2-point complex transform of the samples read as
+ * N/2 complex pairs runs on launches of its own, one single pass or a four-step
+ * pair, and one more launch pairs the bins.  All but the single launches have a
+ * workspace of batch * N/2 complex64.  Rank 2: nx an even number in [2, 32768]
+ * and ny in [1, 16384], both with prime factors <= 7, two launches per
+ * direction, the rows of nx/2 pairs with the pairing and the columns, and a
+ * workspace of one half spectrum per image (fft_workspace_bytes; powers of two
+ * use it for the inverse only).  in != out.
+ * Both buffers are device pointers owned
  * by the caller, 8-byte aligned.
  */
 
 /*
- * Create a plan.  Validates *desc, factors each length into radices
- * {16, 8, 4, 2, 3, 5, 7}, chooses the kernels (single pass through LDS, or the
+ * Create a plan.  Validates *desc, factors each length into radices (powers of
+ * two to 32, and products of 2, 3, 5 and 7 to 25), chooses the kernels (single pass through LDS, or the
  * two-pass four-step decomposition for lengths that do not fit on chip, or the
  * MFMA DFT-16 form, or the ragged persistent kernel), builds the twiddle
  * tables in FP64 on the host, rounds them to the kernel precision and uploads

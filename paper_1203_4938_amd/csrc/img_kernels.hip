@@ -241,17 +241,21 @@ __global__ void __launch_bounds__(kImgBlocksPerGroup) k_img_seed(ImgArgs a) {
 // FP32 products' cycles and mostly beside vector instructions), v and c
 // split into hi + lo pieces, and keeps best and
 // second best; where the two are further apart than both roundings together
-// can move them the FP32 decision is the same, and where any of the wave's
-// pattern blocks is not decided by that margin (4 to 12% of the waves on
-// photographs) the wave takes the FP32 products.  The codes are those of
-// the FP32 products bit for bit.
+// can move them the FP32 decision is the same, and the groups of 16 blocks
+// with a pattern block that is not decided by that margin take the FP32
+// products (0.4 to 0.9% of the groups of smooth pictures with noise, k = 16 to
+// 256; whole waves of 64, 2 to 3.5% of them: 1296 us for the 1149 of 16 images
+// of 2048^2).  The codes are those of the FP32 products bit for bit.
 //
-// The margin.  |x - hi| <= 2^-9 |x| and |x - hi - lo| <= 2^-18 |x| per
-// component; the products lo c_lo are left out.  With S = |v| max|c| +
-// max|c|^2 / 2 >= |D|: 3 * 2^-18 S from the pieces, 33 * 2^-24 S from the BF16
-// chain's FP32 sums, 17 * 2^-24 S from the FP32 products', and 2^-18 S
-// for the 5 low bits of D that hold the codeword's row while ranking; the two D
-// of a decision each.  Values that overflow the pieces fail the comparison
+// The margin.  BF16 holds 8 significant bits, so |x - hi| and |lo| are at most
+// 2^-8 |x|, and lo, rounded to 8 bits itself, leaves |x - hi - lo| <= 2^-17 |x|.
+// The products lo c_lo are left out.  Of |v| |c|, which bounds the sum of the
+// products' magnitudes, a D so loses up to 2^-16 with lo c_lo and 2^-17 with
+// each of the two remainders, 512 u in all (u = 2^-24).  With S = |v| max|c| +
+// max|c|^2 / 2 >= |D|, the 51 FP32 sums of the BF16 chain and the 17 of the FP32
+// products count 2 u S each, as if they truncated, and the 5 low bits of D that
+// hold the codeword's row while ranking 62 u S: 198 u S.  Both D of a decision
+// may move by this much.  Values that overflow the pieces fail the comparison
 // and take the FP32 products too.
 //
 // Operand layouts.  32x32x16: lane l supplies A row (l & 31) and B column (l &
@@ -276,7 +280,7 @@ __global__ void __launch_bounds__(kImgBlocksPerGroup) k_img_seed(ImgArgs a) {
 // NI = 0: the codes of every block are written.
 // 16 images of 2048^2, k = 64: FP32 products alone, the vectors scattered into
 // order and read once more, every (codeword, component) sum a loop of its
-// own: 171 us with sums, 125 the codes; 113 and 88 now (50 us is their bytes'
+// own: 171 us with sums, 125 the codes; 112 and 70 now (50 us is their bytes'
 // time: what is left is vector instructions, half of them the ranking's, and
 // the four barriers of a round).
 typedef float img_f4 __attribute__((ext_vector_type(4)));
@@ -338,13 +342,15 @@ __device__ __forceinline__ float min2f(float a, float b) {
 
 // Best codeword of the lane's own block (16 g4 + col of the wave's 64, whose
 // first is `dev`, `nblk` of them in the image) by the FP32 products, 16 blocks
-// at a time: few registers, as it runs seldom.
+// at a time: few registers, as it runs seldom.  Only for the groups of 16 with
+// a block marked in `which` (uniform over the wave); 0 for the others.
 __device__ __forceinline__ int exact_codes(const float *gcb, const float *hneg, int k, int kp,
-                                           const float *dev, int64_t nblk) {
+                                           const float *dev, int64_t nblk, uint64_t which) {
   const int lane = threadIdx.x & 63, col = lane & 15, g4 = lane >> 4;
   int best = 0;
 #pragma unroll 1
   for (int nt = 0; nt < 4; ++nt) {
+    if (!((which >> (16 * nt)) & 0xffffu)) continue;
     const float4 v = 16 * nt + col < nblk
                          ? reinterpret_cast<const float4 *>(dev)[4 * (16 * nt + col) + g4]
                          : make_float4(0.f, 0.f, 0.f, 0.f);
@@ -458,12 +464,11 @@ __global__ void __launch_bounds__(kImgThreads, NI > 8 ? 3 : 4)
   }
   __syncthreads();
 
-  // margin per |v|, and alone: 2 (3 * 2^-18 + 50 * 2^-24 + 2^-18) S, S = |v|
-  // cmax + h, rounded up
+  // margin per |v|, and alone: 2 (512 u |v| cmax + 198 u (|v| cmax + h)), rounded up
   const float hm = fmaxf(fmaxf(hmax[0], hmax[1]), fmaxf(hmax[2], hmax[3]));
   constexpr uint32_t kRowBits = 31u;
-  constexpr float eps = 2.02f * (3.0f / 262144.0f + 50.0f / 16777216.0f + 32.0f / 8388608.0f);
-  const float mv = eps * 1.001f * __builtin_sqrtf(2.0f * hm), mh = eps * hm + 1e-30f;
+  constexpr float ulp = 1.0f / 16777216.0f, ev = 2.02f * 710.0f * ulp, eh = 2.02f * 198.0f * ulp;
+  const float mv = ev * 1.001f * __builtin_sqrtf(2.0f * hm), mh = eh * hm + 1e-30f;
 
   float gs[ACC ? NI : 1];  // running sums of codewords (tid >> 4) + 16 i, component tid & 15
   int gn[ACC ? NI : 1];    // their counts
@@ -573,7 +578,9 @@ __global__ void __launch_bounds__(kImgThreads, NI > 8 ? 3 : 4)
       // many at once (equal codewords, say): the wave stays with FP32
       if (__popcll(undecided) > 16) fp32_only = true;
       const int64_t b0 = r0 + 64 * wave;
-      best = exact_codes(gcb, hneg, k, kp, a.dev + 16 * (img * a.nb + b0), a.nb - b0);
+      const int exact = exact_codes(gcb, hneg, k, kp, a.dev + 16 * (img * a.nb + b0), a.nb - b0,
+                                    undecided);
+      best = open ? exact : best;
     }
     if constexpr (ACC) {
       const int rank = pat ? atomicAdd(&wcnt[wave * ly.k4 + best], 1) : 0;

@@ -468,7 +468,8 @@ __global__ void __launch_bounds__(kImgThreads, NI > 8 ? 3 : 4)
   const float hm = fmaxf(fmaxf(hmax[0], hmax[1]), fmaxf(hmax[2], hmax[3]));
   constexpr uint32_t kRowBits = 31u;
   constexpr float ulp = 1.0f / 16777216.0f, ev = 2.02f * 710.0f * ulp, eh = 2.02f * 198.0f * ulp;
-  const float mv = ev * 1.001f * __builtin_sqrtf(2.0f * hm), mh = eh * hm + 1e-30f;
+  // (cmax from h, whose squares underflow below 1e-18: what that hides is added)
+  const float mv = ev * 1.001f * (__builtin_sqrtf(2.0f * hm) + 1e-18f), mh = eh * hm + 1e-30f;
 
   float gs[ACC ? NI : 1];  // running sums of codewords (tid >> 4) + 16 i, component tid & 15
   int gn[ACC ? NI : 1];    // their counts

@@ -98,6 +98,10 @@ def test_pieces_bound():
 @pytest.mark.parametrize("k", [2, 28, 64])
 @pytest.mark.parametrize("a,b", [(256.0, 1.0), (8.0, 1.0), (2.0 ** 20, 8.0), (2.0 ** -9, 2.0 ** -12)])
 def test_undecided_pairs(k, a, b):
+    _check_pairs(k, a, b)
+
+
+def _check_pairs(k, a, b):
     import torch
 
     import paper_1203_4938_amd as dp
@@ -118,3 +122,10 @@ def test_undecided_pairs(k, a, b):
     say(f"[margin] k={k} a={a:g} b={b:g}: {n} pairs, {int((d[:, 1] > d[:, 0]).sum())} misjudged by "
         f"the pieces, {bad} wrong codes")
     assert bad == 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("a,b", [(256.0, 2.0 ** -80), (1.0, 2.0 ** -72), (2.0 ** 30, 2.0 ** -70)])
+def test_tiny_codewords(a, b):
+    """Codewords whose squared norm is zero in FP32."""
+    _check_pairs(33, a, b)

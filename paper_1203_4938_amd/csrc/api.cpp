@@ -754,13 +754,20 @@ fft_status_t plan_pow2_2d(dpfft_plan_s *P) {
   return FFT_OK;
 }
 
+// Radix plan of a line of L points that a workgroup reads by `map` and writes
+// by `omap`.
+bool line_radices(int64_t L, int map, int omap, MixedPlan *mp, int order = 0) {
+  const int tmin = map != ELEM_FAST ? 1 : omap == ELEM_FAST ? mixed_rows_tmin(L) : mixed_row_tmin(L);
+  return mixed_radices(L, mp, order, 1024, tmin);
+}
+
 // A runtime-radix step over lines of length L, C lines per workgroup (`stream`:
 // a four-step column step writes whole 128-byte lines).
 std::unique_ptr<MixedStep> make_mixed(dpfft_plan_s *P, const char *name, int64_t L, int map,
                                       int omap, bool tw4, int C, bool stream = false) {
   auto s = std::make_unique<MixedStep>();
   const Override ov = read_override();
-  if (!mixed_radices(L, &s->a.mp, ov.order > 0 ? ov.order : 0)) return nullptr;
+  if (!line_radices(L, map, omap, &s->a.mp, ov.order > 0 ? ov.order : 0)) return nullptr;
   s->a.mp.C = C;
   s->map = map;
   s->omap = omap;
@@ -783,7 +790,7 @@ std::unique_ptr<MixedStep> make_mixed(dpfft_plan_s *P, const char *name, int64_t
 // and one CU's LDS allow, 0 if not even one fits.
 int mixed_lines_max(int64_t L, int map, int omap, bool tw4 = false) {
   MixedPlan mp{};
-  if (!mixed_radices(L, &mp)) return 0;
+  if (!line_radices(L, map, omap, &mp)) return 0;
   for (mp.C = 1024 / mp.T; mp.C > 0; --mp.C)
     if (mixed_lds_bytes(mp, map, omap, tw4) <= kLdsBytes) break;
   return mp.C;
@@ -796,7 +803,7 @@ int mixed_lines_max(int64_t L, int map, int omap, bool tw4 = false) {
 // points 51 us at 1 line (64 threads), 55 at 4.
 int mixed_row_lines(int64_t L) {
   MixedPlan mp{};
-  if (!mixed_radices(L, &mp)) return 0;
+  if (!line_radices(L, ELEM_FAST, ELEM_FAST, &mp)) return 0;
   const int cmax = mixed_lines_max(L, ELEM_FAST, ELEM_FAST);
   int best = std::min(cmax, 1);
   double best_score = -1e9;
@@ -819,7 +826,7 @@ int mixed_col_lines(int64_t L, int map, bool tw4 = false) {
   const int omap = LINE_FAST;
   const int cmax = mixed_lines_max(L, map, omap, tw4);
   MixedPlan mp{};
-  if (!mixed_radices(L, &mp)) return 0;
+  if (!line_radices(L, map, omap, &mp)) return 0;
   for (mp.C = 16; mp.C >= 4; mp.C /= 2)
     if (mp.C <= cmax && 2 * mixed_lds_bytes(mp, map, omap, tw4) <= kLdsBytes) return mp.C;
   int C = 8;

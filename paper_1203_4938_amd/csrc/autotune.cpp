@@ -234,7 +234,7 @@ std::vector<std::string> candidates(const fft_desc_t *d) {
   for (int order : {0, 1}) {
     if (N <= 16384) {
       MixedPlan mp{};
-      if (!mixed_radices(N, &mp, order)) continue;
+      if (!mixed_radices(N, &mp, order, 1024, mixed_rows_tmin(N))) continue;
       for (int C = 1; C * mp.T <= 1024; C *= 2)
         out.push_back("o=" + std::to_string(order) + " c0=" + std::to_string(C));
     } else {

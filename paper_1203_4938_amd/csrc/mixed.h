@@ -40,10 +40,31 @@ struct MixedArgs {
   uint32_t flags;
 };
 
-// Host: radix plan of a 7-smooth L (radix_plan of mixed_plan.h) with at most
+// Fewest threads per line of short rows, whose lanes load T neighbouring
+// elements at a time: with few threads a wave touches many lines at once and
+// its L1 loses them before their next elements.  Without the bound a line of 10
+// to 25 points is one radix of one thread (4 M points, no bound and bound: 12
+// points 26.6 us, 20.2; 18, 29.5 and 19.4; 24, 30.0 and 18.7; 25, 31.2 and 21.4;
+// 64 M points of 24, 468 us and 324).  20 points keep two threads: three do not
+// divide 5 x 4 (64 M points 7% slower).
+constexpr int mixed_row_tmin(int64_t L) { return L < 10 ? 1 : L > 16 && L != 20 ? 3 : 2; }
+
+// The same for batches of rows, where it shows up to 360 points (4 M points: 56
+// points 18.7 us, 16.1; 80, 19.2 and 17.4; 120, 20.4 and 15.9; 64 M points of 288,
+// 232 and 184), as the most points per thread.  Longer lines have enough
+// threads, and a bound would cost them the wide radices (375 points: 38 threads
+// take 20% more than 25); so would 10 points per thread at 98 and 105 (14 x 7
+// and 15 x 7 from 7 and 8 threads: 10% and 15%) and at 48 (12 x 4, 8%).
+constexpr int mixed_rows_tmin(int64_t L) {
+  const int64_t most = L <= 48 ? 12 : L <= 96 ? 10 : L <= 120 ? 14 : 20;
+  const int t = L <= 360 ? (int)((L + most - 1) / most) : 1;
+  return t > mixed_row_tmin(L) ? t : mixed_row_tmin(L);
+}
+
+// Host: radix plan of a 7-smooth L (radix_plan of mixed_plan.h) with tmin to
 // tmax threads per line; order 0: largest radix first, 1: smallest first.
-// Returns false if L has a prime factor above 7 or no plan within tmax.
-bool mixed_radices(int64_t L, MixedPlan *mp, int order = 0, int tmax = 1024);
+// Returns false if L has a prime factor above 7 or no plan within those.
+bool mixed_radices(int64_t L, MixedPlan *mp, int order = 0, int tmax = 1024, int tmin = 1);
 
 // Host: whether every pass's butterflies are owned by the plan's threads.
 bool mixed_covers(const MixedPlan &mp);

@@ -129,14 +129,14 @@ const void *mixed_real_kernel(bool inverse) {
 // ---------------------------------------------------------------------------
 // host helpers
 // ---------------------------------------------------------------------------
-bool mixed_radices(int64_t L, MixedPlan *mp, int order, int tmax) {
+bool mixed_radices(int64_t L, MixedPlan *mp, int order, int tmax, int tmin) {
   if (L < 1 || L > kMixedMaxLine) return false;
   for (int64_t n = L; n > 1;) {
     const int p = n % 2 == 0 ? 2 : n % 3 == 0 ? 3 : n % 5 == 0 ? 5 : n % 7 == 0 ? 7 : 0;
     if (!p) return false;
     n /= p;
   }
-  const RadixPlan r = radix_plan((int)L, order, tmax);
+  const RadixPlan r = radix_plan((int)L, order, tmax, tmin);
   if (r.T == 0) return false;
   mp->L = (int32_t)L;
   mp->P = r.P;

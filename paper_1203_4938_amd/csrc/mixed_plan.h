@@ -77,7 +77,7 @@ constexpr int64_t plan_cost(int L, const int *R, int P, int T) {
 }
 
 struct Search {
-  int L, tmax;
+  int L, tmax, tmin;
   RadixPlan best;
   int R[kMaxPasses] = {};
   // all multisets of `left` radices, none before kMixedRadices[i0], with product n
@@ -100,7 +100,7 @@ struct Search {
     for (int p = 0; p < P; ++p)
       for (int q = 1; q <= mixed_qmax(R[p]); ++q) {
         const int T = ceil_div(L / R[p], q);
-        if (T > tmax) continue;
+        if (T > tmax || T < tmin) continue;
         const int64_t c = plan_cost(L, R, P, T);
         if (c < 0 || (best.cost >= 0 && c >= best.cost)) continue;
         best.cost = c;
@@ -112,18 +112,18 @@ struct Search {
 };
 }  // namespace rplan
 
-// The plan of a 7-smooth L with at most tmax threads per line (tmax >=
+// The plan of a 7-smooth L with tmin to tmax threads per line (tmax >=
 // ceil(L / 16)): the cheapest of the fewest passes, or of one pass more where
 // those leave much of a CU unused.  Largest radix first (the first pass has no
 // twiddles); order 1 takes the same radices smallest first.  P = 0 with T = 0
 // if there is none (L = 1 has P = 0 and T = 1).
-constexpr RadixPlan radix_plan(int L, int order, int tmax) {
+constexpr RadixPlan radix_plan(int L, int order, int tmax, int tmin = 1) {
   if (L == 1) {
     RadixPlan one;
     one.T = 1;
     return one;
   }
-  rplan::Search s{L, tmax, {}};
+  rplan::Search s{L, tmax, tmin, {}};
   int P = 1;
   for (; P <= kMaxPasses && s.best.cost < 0; ++P) s.run(L, 0, 0, P);
   // a pass more may need fewer threads, and so leave less of a CU unused:

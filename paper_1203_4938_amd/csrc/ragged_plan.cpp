@@ -302,7 +302,8 @@ bool fits_big(int64_t L) { return L <= 16 * kRaggedBigThreads && line_elems(L) <
 // radix plan of a line: lines that fit a 256-thread workgroup take at most
 // its threads
 bool ragged_radices(int64_t L, MixedPlan *mp, int order) {
-  return mixed_radices(L, mp, order, fits_single(L) ? kRaggedThreads : kRaggedBigThreads);
+  return mixed_radices(L, mp, order, fits_single(L) ? kRaggedThreads : kRaggedBigThreads,
+                       mixed_row_tmin(L));
 }
 
 }  // namespace

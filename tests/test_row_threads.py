@@ -1,0 +1,48 @@
+"""Threads and lines of short rows: no line of 10 or more points on one thread;
+then the same plans' results."""
+import re
+
+import numpy as np
+import pytest
+
+import synth
+
+SHORT = [n for n in synth.smooth_sizes(3, 360) if n & (n - 1)]
+
+
+def _rows(**kw):
+    """(points, lines per workgroup, threads, grid) of the plan's first launch."""
+    import paper_1203_4938_amd as dp
+    d, keep = dp.make_desc(**kw)
+    st, text = dp.fft_plan_dry(d)
+    assert st == dp.FFT_OK, text
+    m = re.search(r"L=(\d+) .*?C=(\d+) threads=(\d+) grid=(\d+)", text.splitlines()[1])
+    return tuple(int(v) for v in m.groups())
+
+
+def test_threads_of_short_rows():
+    for n in SHORT:
+        most = 9 if n < 10 else 12 if n <= 48 else 10 if n <= 96 else 14 if n <= 120 else 20
+        L, C, threads, _ = _rows(n=n, batch=1000)
+        assert L == n and threads % C == 0 and n <= most * (threads // C), n
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [5, 9, 10, 12, 14, 15, 18, 20, 21, 24, 25, 27, 28, 48, 49, 56, 60, 96,
+                               98, 105, 120, 126, 144, 288, 360])
+def test_short_rows(n, monkeypatch):
+    """A ragged last workgroup, with the lines of small and of large batches."""
+    import oracle
+    import paper_1203_4938_amd as dp
+    from gpu_util import TOL_FP32, max_rel, run_plan, say, to_dev
+    batch = 517
+    x = synth.uniform_complex(synth.BASE_SEED + 830 + n, n, batch)
+    xd = to_dev(x)
+    _, C, threads, _ = _rows(n=n, batch=batch)
+    for c in (C, 256 // (threads // C)):
+        monkeypatch.setenv("DPFFT_FORCE_PLAN", f"c0={c}")
+        p = dp.Plan(n, batch)
+        for inv in (False, True):
+            e = max_rel(run_plan(p, xd, inverse=inv).cpu().numpy(), oracle.fft_batch(x, inverse=inv))
+            say(f"[short rows] n={n} C={c} inverse={inv}: {e:.3e}")
+            assert e <= TOL_FP32, (n, c, inv, e)

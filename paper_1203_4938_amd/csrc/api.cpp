@@ -801,10 +801,17 @@ int mixed_lines_max(int64_t L, int map, int omap, bool tw4 = false) {
 // overlap each other's loads, passes and stores: 3000 points, 16384 lines, 1
 // line per workgroup (167 threads) 176 us, 3 lines 195, 6 lines 250; 960
 // points 51 us at 1 line (64 threads), 55 at 4.
-int mixed_row_lines(int64_t L) {
+// Lines of few threads in batches that the 256 MiB last-level cache does not
+// hold, in and out (`lines` of them, 0: not said), take 256 threads instead: 64 M
+// points of 28, 317 us by the rule above and 238 so; 45, 304 and 247; 112, 218 and
+// 191; 24 M points already 4 to 20% less.  16 M points (256 MiB) take 0 to 16% more,
+// and lines of more than 12 threads gain nothing (192 points of 16 threads 3%).
+constexpr int64_t kLlcBytes = int64_t(256) << 20;
+int mixed_row_lines(int64_t L, int64_t lines = 0) {
   MixedPlan mp{};
   if (!line_radices(L, ELEM_FAST, ELEM_FAST, &mp)) return 0;
   const int cmax = mixed_lines_max(L, ELEM_FAST, ELEM_FAST);
+  if (mp.T <= 12 && 16 * L * lines > kLlcBytes) return std::min(cmax, 256 / mp.T);
   int best = std::min(cmax, 1);
   double best_score = -1e9;
   for (int C = 1; C <= cmax; ++C) {
@@ -903,7 +910,7 @@ bool mixed_fourstep_steps(dpfft_plan_s *P, int64_t N, int64_t B, int64_t in_b, i
 fft_status_t plan_mixed_2d(dpfft_plan_s *P) {
   const int64_t NY = P->ny, NX = P->nx, B = P->batch, D = P->dist;
   const Override ov = read_override();
-  const int CR = mixed_c(ov, 0, mixed_row_lines(NX), NX, ELEM_FAST, ELEM_FAST);
+  const int CR = mixed_c(ov, 0, mixed_row_lines(NX, B * NY), NX, ELEM_FAST, ELEM_FAST);
   const int CC = mixed_c(ov, 1, mixed_col_lines(NY, LINE_FAST), NY, LINE_FAST, LINE_FAST);
   auto r = CR ? make_mixed(P, "mixed_rows", NX, ELEM_FAST, ELEM_FAST, false, CR) : nullptr;
   auto c = CC ? make_mixed(P, "mixed_columns", NY, LINE_FAST, LINE_FAST, false, CC) : nullptr;
@@ -938,7 +945,7 @@ fft_status_t plan_mixed_1d(dpfft_plan_s *P) {
   const int64_t N = P->n, B = P->batch, D = P->dist;
   const Override ov = read_override();
   if (N <= kSinglePassMax) {
-    int C = mixed_row_lines(N);
+    int C = mixed_row_lines(N, B);
     if (ov.c[0] > 0) {
       const int cmax = mixed_lines_max(N, ELEM_FAST, ELEM_FAST);
       if (ov.c[0] > cmax) return fail(FFT_E_UNSUPPORTED, "override c0 too large for N");

@@ -1,5 +1,6 @@
-"""Threads and lines of short rows: no line of 10 or more points on one thread;
-then the same plans' results."""
+"""Threads and lines of short rows: no line of 10 or more points on one thread
+and whole 256-thread workgroups for batches beyond the last-level cache; then
+the same plans' results."""
 import re
 
 import numpy as np
@@ -25,6 +26,17 @@ def test_threads_of_short_rows():
         most = 9 if n < 10 else 12 if n <= 48 else 10 if n <= 96 else 14 if n <= 120 else 20
         L, C, threads, _ = _rows(n=n, batch=1000)
         assert L == n and threads % C == 0 and n <= most * (threads // C), n
+
+
+def test_lines_beyond_the_cache():
+    for n in SHORT:
+        for points in (1 << 24, (1 << 24) + n):  # 256 MiB in and out, and one line more
+            L, C, threads, grid = _rows(n=n, batch=points // n)
+            T = threads // C
+            large = n * (points // n) > 1 << 24
+            assert grid == -(-(points // n) // C)
+            if large and T <= 12:
+                assert C == 256 // T, (n, C, T)
 
 
 @pytest.mark.gpu

@@ -915,12 +915,15 @@ fft_status_t plan_mixed_2d(dpfft_plan_s *P) {
   auto r = CR ? make_mixed(P, "mixed_rows", NX, ELEM_FAST, ELEM_FAST, false, CR) : nullptr;
   auto c = CC ? make_mixed(P, "mixed_columns", NY, LINE_FAST, LINE_FAST, false, CC) : nullptr;
   if (!r || !c) return fail(FFT_E_UNSUPPORTED, "no runtime-radix 2D kernels for this shape");
-  r->a.in_b = r->a.out_b = D;
+  // the rows of images without gaps are one list, tiled through: by image, 64
+  // rows in tiles of 21 (45 points, 256 MiB) 160 us against 129
+  const bool dense = D == NY * NX;
+  r->a.in_b = r->a.out_b = dense ? 0 : D;
   r->a.in_l = r->a.out_l = NX;
   r->a.in_e = r->a.out_e = 1;
-  r->a.lines = NY;
-  r->a.tiles_per_batch = (NY + r->a.mp.C - 1) / r->a.mp.C;
-  r->grid = dim3((unsigned)(B * r->a.tiles_per_batch));
+  r->a.lines = dense ? B * NY : NY;
+  r->a.tiles_per_batch = (r->a.lines + r->a.mp.C - 1) / r->a.mp.C;
+  r->grid = dim3((unsigned)((dense ? 1 : B) * r->a.tiles_per_batch));
   r->first = true;
   r->src = BUF_IN;
   r->dst = BUF_OUT;

@@ -1,6 +1,6 @@
-"""Threads and lines of short rows: no line of 10 or more points on one thread
-and whole 256-thread workgroups for batches beyond the last-level cache; then
-the same plans' results."""
+"""Threads and lines of short rows: no line of 10 or more points on one thread,
+whole 256-thread workgroups for batches beyond the last-level cache, and the
+rows of images without gaps tiled as one list; then the same plans' results."""
 import re
 
 import numpy as np
@@ -39,6 +39,14 @@ def test_lines_beyond_the_cache():
                 assert C == 256 // T, (n, C, T)
 
 
+def test_rows_of_dense_images_are_one_list():
+    for ny, nx, b in ((64, 45, 100), (7, 18, 9), (64, 120, 300), (3, 1000, 5)):
+        L, C, _, grid = _rows(rank=2, shape=(ny, nx), batch=b)
+        assert grid == -(-ny * b // C), (ny, nx, b)
+        L, C, _, grid = _rows(rank=2, shape=(ny, nx), batch=b, dist=ny * nx + 3)
+        assert grid == b * -(-ny // C), (ny, nx, b)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("n", [5, 9, 10, 12, 14, 15, 18, 20, 21, 24, 25, 27, 28, 48, 49, 56, 60, 96,
                                98, 105, 120, 126, 144, 288, 360])
@@ -58,3 +66,39 @@ def test_short_rows(n, monkeypatch):
             e = max_rel(run_plan(p, xd, inverse=inv).cpu().numpy(), oracle.fft_batch(x, inverse=inv))
             say(f"[short rows] n={n} C={c} inverse={inv}: {e:.3e}")
             assert e <= TOL_FP32, (n, c, inv, e)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("ny,nx,b", [(5, 45, 9), (64, 18, 3), (7, 120, 4), (3, 1000, 2)])
+@pytest.mark.parametrize("gap", [0, 5])
+def test_rows_of_images(ny, nx, b, gap):
+    import torch
+
+    import oracle
+    import paper_1203_4938_amd as dp
+    from gpu_util import TOL_FP32
+    x = synth.uniform_complex(synth.BASE_SEED + 840 + nx, ny * nx, b)
+    D = ny * nx + gap
+    buf = torch.zeros(b * D, dtype=torch.complex64, device="cuda")
+    for i in range(b):
+        buf[i * D:i * D + ny * nx] = torch.from_numpy(x[i]).cuda()
+    d, keep = dp.make_desc(rank=2, shape=(ny, nx), batch=b, dist=D if gap else 0)
+    st, h = dp.fft_plan(d)
+    assert st == dp.FFT_OK, dp.fft_last_error()
+    try:
+        for inv in (False, True):
+            out = torch.full_like(buf, 3.0)
+            st = dp.fft_exec(h, buf.data_ptr(), out.data_ptr(),
+                             dp.FFT_INVERSE if inv else dp.FFT_FORWARD)
+            assert st == dp.FFT_OK, dp.fft_last_error()
+            torch.cuda.synchronize()
+            y = out.cpu().numpy()
+            ref = oracle.fft2d(x.reshape(b, ny, nx), inverse=inv)
+            for i in range(b):
+                got = y[i * D:i * D + ny * nx].reshape(ny, nx)
+                e = np.linalg.norm(got - ref[i]) / np.linalg.norm(ref[i])
+                assert e <= TOL_FP32, (inv, i, e)
+                if gap and i + 1 < b:
+                    assert (y[i * D + ny * nx:(i + 1) * D] == 3.0).all()
+    finally:
+        dp.fft_destroy(h)

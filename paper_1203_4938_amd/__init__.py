@@ -131,12 +131,21 @@ def fft_plan(desc: FftDesc, stream: int = 0) -> tuple[int, Optional[int]]:
 
 def fft_exec(handle: int, in_ptr: int, out_ptr: int, direction: int, workspace: int = 0,
              stream: int = 0) -> int:
-    # (argtypes convert the integers; wrapping each in a c_void_p first costs 1 us)
+    # The argument types take integers as they are (wrapping each in a c_void_p
+    # costs 1 us), but also strings, bytes and arrays, as pointers to host
+    # memory: c_void_p, which refuses these, takes what is not an integer.
+    if not (type(handle) is type(in_ptr) is type(out_ptr) is type(workspace) is type(stream) is int):
+        handle, in_ptr, out_ptr, workspace, stream = map(
+            ctypes.c_void_p, (handle, in_ptr, out_ptr, workspace, stream))
     return _lib.fft_exec(handle, in_ptr, out_ptr, direction, workspace, stream)
 
 
 def fft_conv_exec(handle: int, in_ptr: int, filter_ptr: int, filter_dist: int, out_ptr: int,
                   workspace: int = 0, stream: int = 0) -> int:
+    if not (type(handle) is type(in_ptr) is type(filter_ptr) is type(out_ptr) is type(workspace)
+            is type(stream) is int):  # (see fft_exec)
+        handle, in_ptr, filter_ptr, out_ptr, workspace, stream = map(
+            ctypes.c_void_p, (handle, in_ptr, filter_ptr, out_ptr, workspace, stream))
     return _lib.fft_conv_exec(handle, in_ptr, filter_ptr, int(filter_dist), out_ptr, workspace,
                               stream)
 

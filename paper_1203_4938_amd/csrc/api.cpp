@@ -522,21 +522,24 @@ bool choose_line(int L, int map, int omap, bool tw4, int cmax, int step, int64_t
       *out = k;
     }
   }
-  // A column or transposed-row launch of fewer tiles than CUs takes the widest
-  // narrower tile that gives every CU one, or the narrowest there is.  Measured
-  // (whole transform, tiles of 16, 8, 4): 2^18 points alone 14.2, 11.9, 11.6 us,
-  // 4 of them 16.1, 14.1, 16.7; 2^20 alone 24.2, 19.9, 19.7, 2 of them 28.9,
-  // 26.9, 28.5, 4 of them (256 tiles of 16) 32.1, 32.4, 35.5.
+  // A column or transposed-row launch of few tiles takes the narrowest that
+  // still give no CU a second one: what one workgroup moves then sets the
+  // launch's time.  Both directions of the whole transform, wide tiles and these:
+  // 2^16 points alone 19.5 us, 15.3; 2^18 28.2, 21.1, 3 of them (96 tiles of 16) 31.7,
+  // 27.1 in tiles of 8 and 29.6 in tiles of 4; 2^20 alone 47.2, 37.7; 512 x 16 alone
+  // 19.2, 16.4.  From half as many wide tiles as CUs on, the second tiles cost what
+  // the narrower ones gain: 3 of 2^20 (192 tiles of 16) 55.2, 56.5; 3 of 2048 x
+  // 512 (192 of 8) 55.4, 56.7 to 70.  Less than a wave of lanes gains nothing
+  // (2^15 points: columns of 128 in tiles of 8 14.6, of 4 14.8), nor do fewer
+  // tiles of short columns than XCDs (128 x 16 11.5, 12.2; 256 x 16 13.8, 14.2).
   const bool tiles_free = ov.c[step] < 0 && ov.p[step] < 0 && ov.t[step] < 0 && ov.h[step] < 0;
   auto tiles = [&](int C) { return (lines_total + C - 1) / C; };
   if (best >= 0 && tiles_free && (map == LINE_FAST || omap == LINE_FAST) &&
-      tiles(out->lines) < t_cus) {
-    const int wide = out->lines;
+      (L > 256 || tiles(out->lines) >= 8)) {
     for (int i = 0; i < n; ++i) {
       const KernelInfo &k = cand[i];
-      if (k.persistent || k.ept != 16 || k.sub != 1 || k.lines >= wide) continue;
-      const bool fills = tiles(k.lines) >= t_cus, filled = tiles(out->lines) >= t_cus;
-      if (fills ? (!filled || k.lines > out->lines) : (!filled && k.lines < out->lines)) *out = k;
+      if (k.persistent || k.ept != 16 || k.sub != 1 || k.threads < 64) continue;
+      if (k.lines < out->lines && tiles(k.lines) <= t_cus) *out = k;
     }
   }
   return best >= 0;

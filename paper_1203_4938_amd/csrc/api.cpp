@@ -538,7 +538,7 @@ bool choose_line(int L, int map, int omap, bool tw4, int cmax, int step, int64_t
       (L > 256 || tiles(out->lines) >= 8)) {
     for (int i = 0; i < n; ++i) {
       const KernelInfo &k = cand[i];
-      if (k.persistent || k.ept != 16 || k.sub != 1 || k.threads < 64) continue;
+      if (k.persistent || !k.exact || k.sub != 1 || k.threads < 64) continue;
       if (k.lines < out->lines && tiles(k.lines) <= t_cus) *out = k;
     }
   }

@@ -322,7 +322,11 @@ constexpr int pf_tw_entries() {
 // LDS already carries three exchanges), hence the exclusion.  The copy is
 // published by the barrier of the first exchange, which precedes the first
 // pass with twiddles.
-template <int L, int C, int MAP, int OMAP, int EPT, int NTH>
+// EXACT (the narrow tiles): only forms whose twiddles are table entries, as the
+// wide tiles' are.  What the occupancy rule gives a narrow tile, one product of
+// two entries per twiddle, raised the error of 256-, 512- and 2048-point columns
+// by 10 to 20%, and workgroups are too few there for the LDS to matter.
+template <int L, int C, int MAP, int OMAP, int EPT, int NTH, bool EXACT = false>
 struct PlainTw {
   static constexpr int kLds = 160 * 1024;
   static constexpr int BASE = lds_pairs<L, C, MAP, OMAP>() * 8;
@@ -336,12 +340,17 @@ struct PlainTw {
   static constexpr int FIRST_N = pf_first_entries<L, EPT>();
   // 0: global table, 1: per-pass table, 2: first pass's table + two-level, 3: two-level
   static constexpr int MODE = P2<L, EPT>::NP < 2                        ? 0
+                              : EXACT ? (DIRECT_N > 0 && BASE + DIRECT_N * 8 <= kLds            ? 1
+                                         : P2<L, EPT>::NP == 2 && BASE + (N2L + FIRST_N) * 8 <= kLds ? 2
+                                                                                                 : 0)
                               : (DIRECT_N > 0 && fits(DIRECT_N))         ? 1
                               : OMAP != MAP                              ? 0
                               : (FIRST_N > 0 && fits(N2L + FIRST_N))     ? 2
                               : fits(N2L)                                ? 3
                                                                          : 0;
   static constexpr int NTW = MODE == 1 ? DIRECT_N : MODE == 2 ? N2L + FIRST_N : MODE == 3 ? N2L : 0;
+  // every twiddle is one table entry
+  static constexpr bool IS_EXACT = MODE <= 1 || (MODE == 2 && P2<L, EPT>::NP == 2);
   using type = std::conditional_t<
       MODE == 0, TwTable,
       std::conditional_t<MODE == 1, TwLdsTable, std::conditional_t<MODE == 2, TwLdsFirst, TwLds2>>>;

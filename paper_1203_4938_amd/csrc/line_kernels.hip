@@ -74,7 +74,7 @@ __global__ void __launch_bounds__(C * (P2<L, EPT>::T))
     for (int m = 0; m < E; ++m) v[m] = make_float2(0.0f, 0.0f);
   }
 
-  using PT = PlainTw<L, C, MAP, OMAP, EPT, C * G::T>;
+  using PT = PlainTw<L, C, MAP, OMAP, EPT, C * G::T, (NT & 4) != 0>;
   // Four-step twiddle bases.  Where two or more workgroups share a CU, their
   // table entries are loaded before the passes, so that the latency passes
   // behind them instead of before the stores (the 256-point column tiles of
@@ -474,6 +474,7 @@ struct LineEntry {
   bool pf;
   bool pref;          // the planner's default for its shape (measured fastest)
   int ept;
+  bool exact = false; // plain tiles: every pass twiddle is one table entry
   int sub = 1;        // sub-lines per line (2: k_lines_half)
 };
 
@@ -483,8 +484,9 @@ struct LineEntry {
             (int)sizeof(cf) * lds_pairs<L_, C_, M_, O_>() +                         \
                 (int)sizeof(cf) * (KPF ? pf_tw_entries<L_, C_, M_, O_, KEPT>()        \
                                        : PlainTw<L_, C_, M_, O_, KEPT,                \
-                                                 C_ * P2<L_, KEPT>::T>::NTW),         \
-            KPF, KPREF, KEPT}
+                                                 C_ * P2<L_, KEPT>::T, (KNT & 4) != 0>::NTW), \
+            KPF, KPREF, KEPT,                                                         \
+            !KPF && PlainTw<L_, C_, M_, O_, KEPT, C_ * P2<L_, KEPT>::T, (KNT & 4) != 0>::IS_EXACT}
 
 // rows: forward, inverse single pass (swap in+out), 2D row pass inverse (swap in)
 #define ROW(L_, C_)                                                                          \
@@ -530,11 +532,16 @@ static const LineEntry kLineTable[] = {
 // them only there): what one workgroup moves then sets the launch's time (2^20
 // points alone, 1024 x 1024: tiles of 16 10.1 + 10.8 us, tiles of 4 below 8 each).
 static const LineEntry kLineTableNarrow[] = {
-    COL(128, 8), COL(128, 4), COL(256, 8), COL(256, 4), COL(512, 8), COL(512, 4), COL(1024, 4),
-    COLTW(128, 8), COLTW(128, 4), COLTW(256, 8), COLTW(256, 4), COLTW(512, 8), COLTW(512, 4),
-    COLTW(1024, 4), COLTW(2048, 2),
-    ROWT(128, 8), ROWT(128, 4), ROWT(256, 8), ROWT(256, 4), ROWT(512, 8), ROWT(512, 4),
-    ROWT(1024, 4), ROWT(2048, 2),
+    COL(128, 4), COLTW(128, 4), ROWT(128, 8), ROWT(128, 4), ROWT(256, 8), ROWT(256, 4),
+    ROWT(512, 8), ROWT(512, 4), ROWT(1024, 4), ROWT(2048, 2),
+};
+// those whose twiddles would be products keep to the table (see PlainTw)
+#undef KNT
+#define KNT 4
+static const LineEntry kLineTableNarrowExact[] = {
+    COL(128, 8), COL(256, 8), COL(256, 4), COL(512, 8), COL(512, 4), COL(1024, 4),
+    COL(2048, 4), COLTW(128, 8), COLTW(256, 8), COLTW(256, 4), COLTW(512, 8), COLTW(512, 4),
+    COLTW(1024, 4), COLTW(2048, 4), COLTW(2048, 2),
 };
 // nontemporal tile data (rows of 2048, the 256 x 256 four-step): 2-4% faster
 #undef KNT
@@ -642,7 +649,7 @@ static const LineEntry kLineTablePf32x[] = {
   LineEntry{L_, C_, M_, O_, TW_, {F0, F1, F2, F3}, C_ * L_ / (2 * KES),                     \
             (int)sizeof(cf) * lds_pairs<L_ / 2, C_, M_, O_>() +                              \
                 (int)sizeof(cf) * half_tw_entries<L_, C_, M_, O_, KES>(),                     \
-            false, KPREF, KES, 2}
+            false, KPREF, KES, false, 2}
 #define HCOL(L_, C_)                                                                       \
   HENTRY(L_, C_, LINE_FAST, LINE_FAST, false, KH(L_, C_, LINE_FAST, LINE_FAST, false, 0), \
          nullptr, KH(L_, C_, LINE_FAST, LINE_FAST, false, 2),                               \
@@ -678,6 +685,7 @@ static void fill(const LineEntry &e, KernelInfo *out) {
   out->persistent = e.pf;
   out->preferred = e.pref;
   out->ept = e.ept;
+  out->exact = e.exact;
   out->sub = e.sub;
 }
 
@@ -685,6 +693,7 @@ template <class F>
 static void for_each_entry(F f) {
   for (const auto &e : kLineTable) f(e);
   for (const auto &e : kLineTableNarrow) f(e);
+  for (const auto &e : kLineTableNarrowExact) f(e);
   for (const auto &e : kLineTableNt) f(e);
   for (const auto &e : kLineTable32Pref) f(e);
   for (const auto &e : kLineTable32) f(e);
@@ -709,7 +718,7 @@ uint64_t line_registry_digest() {
   };
   for_each_entry([&](const LineEntry &e) {
     mix(e.L), mix(e.C), mix(e.map), mix(e.omap), mix(e.tw4), mix(e.threads), mix(e.lds);
-    mix(e.pf), mix(e.pref), mix(e.ept), mix(e.sub);
+    mix(e.pf), mix(e.pref), mix(e.ept), mix(e.exact), mix(e.sub);
     for (int i = 0; i < 4; ++i) mix(e.fn[i] != nullptr);
   });
   return h;

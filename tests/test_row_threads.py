@@ -102,3 +102,36 @@ def test_rows_of_images(ny, nx, b, gap):
                     assert (y[i * D + ny * nx:(i + 1) * D] == 3.0).all()
     finally:
         dp.fft_destroy(h)
+
+
+FOUR = [16807, 17496, 21609, 28125, 49000, 59049, 84035, 98415, 117649, 174960, 177147, 300000]
+
+
+def test_threads_of_transposed_rows():
+    """Whole 128-byte lines of the intermediate where the threads are few."""
+    import paper_1203_4938_amd as dp
+    for n in FOUR:
+        for real in (False, True):
+            if real and n % 2 == 0:
+                continue
+            d, keep = dp.make_desc(n=2 * n if real else n, batch=3, flags=dp.FFT_F_REAL if real else 0)
+            st, text = dp.fft_plan_dry(d)
+            assert st == dp.FFT_OK
+            rows = re.findall(r"rows_transposed\S*: L=\d+ .*?C=(\d+) threads=(\d+)", text)
+            assert rows
+            for C, threads in rows:
+                T = int(threads) // int(C)
+                assert T >= 64 or T % 16 == 0, (n, T)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", FOUR)
+def test_transposed_rows(n):
+    import oracle
+    import paper_1203_4938_amd as dp
+    from gpu_util import TOL_FP32, max_rel, run_plan, to_dev
+    x = synth.uniform_complex(synth.BASE_SEED + 850, n, 3)
+    p, xd = dp.Plan(n, 3), to_dev(x)
+    for inv in (False, True):
+        e = max_rel(run_plan(p, xd, inverse=inv).cpu().numpy(), oracle.fft_batch(x, inverse=inv))
+        assert e <= TOL_FP32, (n, inv, e)

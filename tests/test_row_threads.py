@@ -135,3 +135,42 @@ def test_transposed_rows(n):
     for inv in (False, True):
         e = max_rel(run_plan(p, xd, inverse=inv).cpu().numpy(), oracle.fft_batch(x, inverse=inv))
         assert e <= TOL_FP32, (n, inv, e)
+
+
+LONG = [n for n in synth.smooth_sizes(3600, 16384) if n & (n - 1)]
+
+
+def test_threads_of_long_rows():
+    """At most four waves to 4096 points; beyond, 16 points per thread where the
+    plan of fewer or more threads leaves no more workgroups on a CU."""
+    for n in LONG:
+        _, C, threads, _ = _rows(n=n, batch=50)
+        T = threads // C
+        assert T <= 256 or n > 4096, n
+        assert T <= 1024
+    for n, T in ((3920, 245), (5103, 319), (6561, 411), (7203, 451), (7875, 493), (12005, 751)):
+        assert _rows(n=n, batch=50)[1:3] == (1, T)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [3920, 4050, 4116, 5103, 6561, 6912, 7203, 7875, 8000, 10240,
+                               12005, 12288, 15309, 16200])
+def test_long_rows(n):
+    import torch
+
+    import oracle
+    import paper_1203_4938_amd as dp
+    from gpu_util import TOL_FP32, max_rel, run_plan, to_dev
+    x = synth.uniform_complex(synth.BASE_SEED + 860, n, 3)
+    p, xd = dp.Plan(n, 3), to_dev(x)
+    for inv in (False, True):
+        e = max_rel(run_plan(p, xd, inverse=inv).cpu().numpy(), oracle.fft_batch(x, inverse=inv))
+        assert e <= TOL_FP32, (n, inv, e)
+    r = np.random.default_rng(n).uniform(-1, 1, (5, 2 * n)).astype(np.float32)
+    q = dp.Plan(2 * n, 5, real=True)
+    spec = q.exec(torch.from_numpy(r).cuda())
+    back = q.exec(spec, inverse=True)
+    torch.cuda.synchronize()
+    ref = oracle.fft_batch(r.astype(np.complex64))[:, : n + 1]
+    assert oracle.rel_l2_f32(spec.cpu().numpy(), ref).max() <= TOL_FP32
+    assert oracle.rel_l2_f32(back.cpu().numpy().astype(np.complex64), r.astype(np.complex128)).max() <= TOL_FP32

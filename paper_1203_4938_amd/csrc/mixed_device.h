@@ -57,11 +57,13 @@ __device__ __forceinline__ cf tw2_lookup(const lcf *t, int shift, uint32_t e) {
 }
 
 // Pass twiddles w_L^{e1 r}, r = 1..R-1, into x[1..R-1] (multiplied in).  From
-// radix 6 on only r = 1, 2, 3 and the multiples of 4 are looked up; the
-// others are products w^{4s} w^{l}, which halves the table reads.
+// radix 10 on only r = 1, 2, 3 and the multiples of 4 are looked up; the others
+// are products w^{4s} w^{l}, which halves the table reads.  Below that the
+// products save little (960 = 15 x 8 x 8 3%, 720 = 20 x 6 x 6 1%) and cost accuracy
+// (343 = 7 x 7 x 7 3%, lines of 512 = 8 x 8 x 8 in 301056 points 6%).
 template <int R>
 __device__ __forceinline__ void apply_pass_twiddles(cf *x, const lcf *t, int shift, uint32_t e1) {
-  if constexpr (R >= 6) {
+  if constexpr (R >= 10) {
     cf wl[4];
 #pragma unroll
     for (int l = 1; l < 4; ++l) {

@@ -80,3 +80,47 @@ def test_autotune_then_plan(kw, tmp_path):
     assert f'override="{choice}"' in r.stdout
     err = float([l for l in r.stdout.splitlines() if l.startswith("err ")][0].split()[1])
     assert err <= 1e-5
+
+
+GRAPH = 4  # FFT_F_GRAPH
+
+CHECK_RAGGED = """
+import sys
+import torch
+sys.path.insert(0, {tests!r})
+import oracle, synth
+import paper_1203_4938_amd as dp
+from gpu_util import to_dev
+sizes = {sizes}
+flat, offs = synth.uniform_ragged(synth.BASE_SEED + 806, sizes)
+p = dp.Plan(ragged_sizes=sizes, graph={graph})
+ref = oracle.fft_ragged(flat, sizes, offs)
+y = p.exec(to_dev(flat)).cpu().numpy()
+torch.cuda.synchronize()
+print("err", max(abs(y[o:o + n] - ref[o:o + n]).max() / abs(ref[o:o + n]).max()
+                 for o, n in zip(offs, sizes)))
+"""
+
+
+@pytest.mark.parametrize("graph", [False, True])
+def test_ragged_batch_is_compared_in_its_own_form(graph, tmp_path):
+    """The tuned and the untuned plan of a ragged batch are compared as the
+    descriptor launches them: as a graph where it asks for one."""
+    env = dict(os.environ)
+    env["DPFFT_TUNE_CACHE"] = str(tmp_path / "tune.json")
+    env.pop("DPFFT_FORCE_PLAN", None)
+    sizes = [120, 1000, 6000, 1000, 343]
+    r = _child(TUNE.format(kw=repr(dict(ragged_sizes=sizes, flags=GRAPH if graph else 0))), env)
+    assert r.returncode == 0, r.stderr
+    last = [l for l in r.stdout.splitlines() if "whole batch" in l]
+    assert len(last) == 1
+    assert ("whole batch as a HIP graph " in last[0]) == graph
+    kept = "heuristic kept" in last[0]
+    entries = json.loads((tmp_path / "tune.json").read_text())["entries"]
+    assert len(entries) == len(set(sizes))
+    assert all(v == "h" for v in entries.values()) == kept
+    r = _child(CHECK_RAGGED.format(sizes=sizes, graph=graph,
+                                   tests=os.path.join(ROOT, "tests")), env)
+    assert r.returncode == 0, r.stderr
+    err = float([l for l in r.stdout.splitlines() if l.startswith("err ")][0].split()[1])
+    assert err <= 1e-5

@@ -56,32 +56,15 @@ __device__ __forceinline__ cf tw2_lookup(const lcf *t, int shift, uint32_t e) {
   return cmul(hi, lo);
 }
 
-// Pass twiddles w_L^{e1 r}, r = 1..R-1, into x[1..R-1] (multiplied in).  From
-// radix 10 on only r = 1, 2, 3 and the multiples of 4 are looked up; the others
-// are products w^{4s} w^{l}, which halves the table reads.  Below that the
-// products save little (960 = 15 x 8 x 8 3%, 720 = 20 x 6 x 6 1%) and cost accuracy
-// (343 = 7 x 7 x 7 3%, lines of 512 = 8 x 8 x 8 in 301056 points 6%).
+// Pass twiddles w_L^{e1 r}, r = 1..R-1, into x[1..R-1] (multiplied in).  All are
+// looked up: products of a few of them halve the table reads and save time (16 M
+// points: 10000 points 7%, 5000 6%, 4000 5%, 2000 4%, 1080 x 1920 images 1%, others
+// 0 to 4%) but cost accuracy (5000 = 25 x 20 x 10 points 8%, 3136 = 16 x 14 x 14 8%, 2000
+// 4%).
 template <int R>
 __device__ __forceinline__ void apply_pass_twiddles(cf *x, const lcf *t, int shift, uint32_t e1) {
-  if constexpr (R >= 10) {
-    cf wl[4];
 #pragma unroll
-    for (int l = 1; l < 4; ++l) {
-      wl[l] = tw2_lookup(t, shift, e1 * (uint32_t)l);
-      x[l] = cmul(x[l], wl[l]);
-    }
-#pragma unroll
-    for (int s = 4; s < R; s += 4) {
-      const cf w4 = tw2_lookup(t, shift, e1 * (uint32_t)s);
-      x[s] = cmul(x[s], w4);
-#pragma unroll
-      for (int l = 1; l < 4; ++l)
-        if (s + l < R) x[s + l] = cmul(x[s + l], cmul(w4, wl[l]));
-    }
-  } else {
-#pragma unroll
-    for (int r = 1; r < R; ++r) x[r] = cmul(x[r], tw2_lookup(t, shift, e1 * (uint32_t)r));
-  }
+  for (int r = 1; r < R; ++r) x[r] = cmul(x[r], tw2_lookup(t, shift, e1 * (uint32_t)r));
 }
 
 // Four-step twiddles w_N^{line (b + r NS)} = A B^r of outputs r = 0..R-1 of

@@ -81,7 +81,7 @@ typedef enum {
 #define FFT_F_NO_AUTOTUNE 2u /* ignore the autotune cache, use the heuristic plan */
 #define FFT_F_GRAPH 4u       /* ragged plans: replay the launches as a HIP graph */
 #define FFT_F_PER_SIZE 8u    /* ragged plans: one launch per distinct length instead of
-                                the two persistent launches (the comparison baseline) */
+                                the batch's shared launches (the comparison baseline) */
 #define FFT_F_REAL 16u       /* real samples (see "Real-input transforms" below) */
 #define FFT_F_CONV 32u       /* the plan also runs fft_conv_exec (circular convolution) */
 
@@ -195,7 +195,9 @@ fft_status_t fft_plan_dry(const fft_desc_t *desc, char *buf, size_t len);
  * pass in a 256- or 1024-thread workgroup or four-step, and the four-step
  * split, each timed on a batch of signals of that length alone (at least
  * 2^21 points); the fastest is recorded for (architecture, length) and used
- * by every later ragged plan containing that length. */
+ * by every later ragged plan containing that length.  The whole batch is then
+ * timed with these and with the heuristic choices, as a HIP graph if the
+ * descriptor has FFT_F_GRAPH; if the latter are faster they are recorded. */
 fft_status_t fft_autotune(const fft_desc_t *desc, void *hip_stream, int reps, char *report,
                           size_t len);
 

@@ -740,8 +740,10 @@ fft_status_t plan_pow2_2d(dpfft_plan_s *P) {
   // 256 MiB last-level cache, which in its own order it would push out first.
   // 1024^2: 64 images 411 us, 381; 32 217, 198; 28 179, 171; 128 785, 751.  Smaller
   // batches stay cached whole and lose (48 images of 1024 x 512, 192 MiB, 130 us,
-  // 137), rows of 2048 points gain nothing (32 images 370, 372), and neither
-  // did the other kernels' pairs of passes.
+  // 137).  Rows of 2048 points are stored non-temporally, so nothing of them is
+  // left in that cache and the order does not matter (32 images 370, 372; other
+  // batches within 0.8%); rows of 128 to 1024 and 4096 to 16384 points gain 1 to
+  // 14%.  The other kernels' pairs of passes gained nothing.
   const bool back = c->k.sub == 2 && 8 * B * D >= int64_t(224) << 20 && NX != 2048;
   c->a.flags = F_REMAP | F_ROUNDS | (back ? F_BACK : 0u);
   c->grid = dim3((unsigned)(B * c->a.tiles_per_batch));
@@ -845,11 +847,16 @@ int mixed_row_lines(int64_t L, int64_t lines = 0) {
 }
 
 // Columns (or transposed rows) per workgroup: 16, so that a row piece is one
-// 128-byte line, where two such workgroups share a CU's LDS, else 8, else 4,
-// else what fits: a workgroup alone on its CU stops its memory traffic while
-// it computes.  46080 = 192 x 240: 16 columns 160 + 143 us, 8 columns 204 +
-// 156; 1080-point columns (16 of them: one workgroup per CU): 142 us at 16,
-// 106 at 8; 1000 x 1000 four-step: 306 + 275 us at 16, 263 + 223 at 8.
+// 128-byte line, where the LDS holds two such workgroups, else 8, else 4, else
+// what fits: a workgroup alone on its CU stops its memory traffic while it
+// computes.  46080 = 192 x 240: 16 columns 160 + 143 us, 8 columns 204 + 156;
+// 1080-point columns, which the LDS holds once at 16: 142 us at 16, 106 at 8;
+// 1000 x 1000 four-step: 306 + 275 us at 16, 263 + 223 at 8.  Only the LDS is
+// counted: workgroups of 9 to 12 waves (560, 1120, 1125, 1152, 1176, 2240, 2304,
+// 2352 and 3920 points) are alone on their CU by their registers (16 waves of
+// them fit), and other widths are faster for some: 560 points, 16 M in all, 87
+// us at 16, 81 at 8, 57 at 6, 60 at 4; 1120, 88 at 8, 67 at 6, 85 at 4; 1152, 84
+// at 8, 80 at 4; 2240, 87 at 4, 84 at 6; 2304, 84 at 4, 95 at 2.
 int mixed_col_lines(int64_t L, int map, bool tw4 = false) {
   const int omap = LINE_FAST;
   const int cmax = mixed_lines_max(L, map, omap, tw4);
@@ -1215,8 +1222,10 @@ std::unique_ptr<MixedRealStep> make_mixed_real(dpfft_plan_s *P, const char *name
 // 128 x 2^19 295 + 294, 239 + 253; 256 x 2^18 275 + 275, 207 + 219; shorter cores
 // leave the other pass lines of 128 points and gain nothing (512 x 2^17 269 +
 // 263, 270 + 253).  Near the line 2 x 2^21 took 38 + 36 and takes 31 + 33, 17 x 2^18
-// 38 + 30 and 28 + 25; smaller batches are bound by their launches' fixed
-// times and keep the three that their plans are described with.
+// 38 + 30 and 28 + 25.  Two launches already win somewhat below it (forward +
+// inverse, two against three: 2^20 core points 0.88 to 0.93, 1.5 x 2^20 0.78 to
+// 0.88, 1.5 x 2^19 1.00 to 1.03, 2^19 1.12 to 1.18); batches under 2^21 keep the
+// three launches that their plans are described with.
 constexpr int64_t kPairInTiles = int64_t(1) << 21;
 
 // Core bytes of a batch for which its rows read the intermediate with
@@ -1294,8 +1303,12 @@ fft_status_t plan_real_fourstep(dpfft_plan_s *P, bool *done) {
 // Signals from which the 7-smooth single-pass core pairs its bins in LDS, one
 // launch and no workspace: 100,000 signals of 70 samples 53 us in two launches,
 // 21 in one, 2000 of 30000 266 us, 200.  Smaller batches keep the
-// core and the pairing launch their plans are described with (3 signals of
-// 1000: 8.9 us either way).
+// core and the pairing launch their plans are described with; one launch would
+// be faster there for short signals and slower for long ones (1 to 3 signals,
+// forward, two launches and one: 6 samples 5.9 us, 3.4; 70, 8.1 and 7.7; 1000, 8.4
+// and 8.2; 10000, 12.0 and 11.9; 30000, 18.8 and 19.1; 32400, 20.7 and 21.3;
+// inverse 6.0 and 3.4, 8.1 and 8.0, 8.5 and 8.6, 12.2 and 12.0, 18.9 and 20.1,
+// 21.0 and 23.0).
 constexpr int64_t kPairInLds = 4;
 
 // Real-input batch of 1D signals: one launch per direction while the

@@ -9,8 +9,9 @@ namespace dpfft {
 constexpr int kMaxPasses = 12;
 
 // Radices with a device pass.  The composite ones run as products of their
-// factors in registers (coprime factors without twiddles), so a line of up to
-// 625 points takes two passes through LDS and one of up to 15625 three.
+// factors in registers (coprime factors without twiddles), so most lines of up
+// to 625 points take two passes through LDS (243, 343, 512 and 560 three) and
+// most of up to 15625 three (11760 four, 12005 five).
 constexpr int kMixedRadices[] = {25, 24, 21, 20, 18, 16, 15, 14, 12, 10, 9, 8, 7, 6, 5, 4, 3, 2};
 constexpr int kNumMixedRadices = sizeof(kMixedRadices) / sizeof(int);
 
